@@ -20,6 +20,7 @@
 #include "felis_internal.h"
 
 #include "erfc_coeffs.h"
+#include "erfc_coeffs_fp64.h"
 #include "restraint.h"
 
 namespace felis {
@@ -101,41 +102,7 @@ __device__ __forceinline__ float3 min_img(const BoxW& B, float dx, float dy, flo
 // The 8 i-atoms of a cluster, wave-uniform (held in scalar registers).
 struct ICluster {
   float x[kClus], y[kClus], z[kClus], q[kClus], sig[kClus], eps[kClus], lig[kClus];
-  int ai[kClus];                            // atom indices (FP64 energies)
 };
-
-// One pair's real-space Coulomb and LJ energies with every term in FP64 (the
-// energy level 2 of the pair kernel): the minimum-image distance from the
-// raw (unwrapped) FP32 coordinates of atoms ai, aj as d - L rint(d (1/L)) and d^2 = (dx^2 + dy^2) + dz^2
-// without contraction, the cutoff r < r_c on r = sqrt(d^2), the window's
-// charges of atoms ai, aj in FP64, Lorentz-Berthelot parameters from the packed (sigma/2,
-// 2 sqrt(eps)) and the softcore form at lambda_vdw for pairs touching the
-// ligand.  Out of line: its registers stay out of the force path.
-__device__ __attribute__((noinline)) void pair_energy_fp64(const LegDev& g, const BoxW& B, size_t base, int ai,
-                                                           int aj, float ligi, float ligj, float hsi, float hsj,
-                                                           float e2i, float e2j, float lam_e, float lam_v,
-                                                           double& ec, double& el) {
-#pragma clang fp contract(off)
-  const size_t oi = base + ai, oj = base + aj;
-  double dx = (double)g.x[oi] - (double)g.x[oj], dy = (double)g.y[oi] - (double)g.y[oj];
-  double dz = (double)g.z[oi] - (double)g.z[oj];
-  dx = dx - B.L[0] * rint(dx * B.invL[0]);
-  dy = dy - B.L[1] * rint(dy * B.invL[1]);
-  dz = dz - B.L[2] * rint(dz * B.invL[2]);
-  const double r2 = (dx * dx + dy * dy) + dz * dz;
-  const double r = sqrt(r2);
-  if (!(r < g.rcd)) return;
-  const bool li = ligi > 0.0f, lj = ligj > 0.0f;
-  const double qa = window_charge_fp64(g, ai, (double)lam_e), qb = window_charge_fp64(g, aj, (double)lam_e);
-  ec += kKE * qa * qb * erfc(g.alphad * r) / r;
-  const double sig = (double)hsi + (double)hsj;
-  const double eps = 0.25 * (double)e2i * (double)e2j;
-  if (eps == 0.0) return;
-  const double lam = (li || lj) ? (double)lam_v : 1.0;
-  const double s2 = sig * sig, s6 = s2 * s2 * s2;
-  const double s = g.sc_alphad * (1.0 - lam) * s6 + r2 * r2 * r2;
-  el += lam * 4.0 * eps * (s6 * s6 / (s * s) - s6 / s);
-}
 
 __device__ __forceinline__ float uniform(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
@@ -163,8 +130,7 @@ template <int ENERGY, int IMG, int HALF>
 __device__ __forceinline__ void sweep(const LegDev& g, const BoxF B, const ICluster& I, gptr<unsigned> ent, int cnt,
                                       gptr<f32x4> xq, gptr<f32x2> pr, int lane,
                                       float lam_v, float a_sc, bool soft_window, float (&fx)[4],
-                                      float (&fy)[4], float (&fz)[4], double& ec, double& el, const BoxW* Bw,
-                                      float lam_e, const int* permw, size_t base) {
+                                      float (&fy)[4], float (&fz)[4], double& ec, double& el) {
   const float Lx = B.L[0], Ly = B.L[1], Lz = B.L[2];
   const float iLx = B.iL[0], iLy = B.iL[1], iLz = B.iL[2];
   const float rc2 = g.rc2, alpha = g.alpha;
@@ -181,7 +147,6 @@ __device__ __forceinline__ void sweep(const LegDev& g, const BoxF B, const IClus
     const unsigned e = e_next;
     const f32x4 xj = xj_next;
     const f32x2 pj = pj_next;
-    const int s = (int)(e >> 8);
     e_next = e_next2;
     const int nidx = it + 128 + lane;
     e_next2 = nidx < cnt ? ent[nidx] : 0u;
@@ -214,8 +179,8 @@ __device__ __forceinline__ void sweep(const LegDev& g, const BoxF B, const IClus
       // list's entries are consecutive in the Hilbert order, so a wave's
       // partners are near one another and often all beyond r_c of one side
       // of the half-cluster); a skipped lane adds nothing, exactly as the
-      // select below would.  The FP64 energy form decides its own cutoff.
-      if (ENERGY < 2 && __ballot(in) == 0ull) continue;
+      // select below would.
+      if (__ballot(in) == 0ull) continue;
       // lanes outside (in == false) may compute inf or NaN below: every
       // result they feed is dropped by the selects on `in`
       const float r2s = r2;
@@ -261,13 +226,10 @@ __device__ __forceinline__ void sweep(const LegDev& g, const BoxF B, const IClus
       fx[k] = fmaf(-fs, dx, fx[k]);
       fy[k] = fmaf(-fs, dy, fy[k]);
       fz[k] = fmaf(-fs, dz, fz[k]);
-      if (ENERGY == 1 && in) {
+      if (ENERGY && in) {
         ec += (double)(qq * (pt * ex) * rinv);
         el += (double)elj;
       }
-      if (ENERGY == 2 && ((e >> k) & 1u))
-        pair_energy_fp64(g, *Bw, base, I.ai[ii], permw[s], I.lig[ii], ligj, I.sig[ii], pj.x, I.eps[ii],
-                         fabsf(pj.y), lam_e, lam_v, ec, el);
     }
   }
 }
@@ -303,10 +265,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   const BoxF B = box_f(g.box[w]);
   const float lam_v = g.lam[4 * w + 1];
   const float a_sc = g.lam[4 * w + 3];
-  const float lam_e = g.lam[4 * w];
   const bool soft_window = lam_v < 1.0f;
-  const BoxW* Bw = &g.box[w];
-  const int* permw = g.perm + (size_t)w * g.npad;
 
   // i-atoms: images nearest the cluster's first atom (always a real atom:
   // padding only follows the last atom), and the cluster's extent
@@ -324,7 +283,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
         if (c * kClus + ii < g.n) ext[d] = fmaxf(ext[d], fabsf(v[d] - r0[d]));
       }
     }
-    if (ENERGY == 2) I.ai[ii] = __builtin_amdgcn_readfirstlane(g.perm[(size_t)w * g.npad + c * kClus + ii]);
     I.x[ii] = v[0]; I.y[ii] = v[1]; I.z[ii] = v[2];
     I.q[ii] = uniform(a.w);
     I.sig[ii] = uniform(p.x);
@@ -339,7 +297,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     inside = inside && x0 - ext[d] - rc >= 0.0f && x0 + ext[d] + rc < B.L[d];
   }
   const int img = inside ? 2 : (shift ? 1 : 0);
-  const size_t base = (size_t)w * g.n;
   // the two half-cluster lists (partners of atoms 0-3, then of atoms 4-7);
   // each half's forces are reduced over the wave before the next half
   const gptr<unsigned> ent = as_global(g.lent + (size_t)item * 2 * g.cap);
@@ -350,7 +307,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
     float fx[4] = {0.f, 0.f, 0.f, 0.f}, fy[4] = {0.f, 0.f, 0.f, 0.f}, fz[4] = {0.f, 0.f, 0.f, 0.f};
     const gptr<unsigned> eh = ent + half * g.cap;
     const int cnt = g.lcount[2 * item + half];
-#define FELIS_SWEEP(M, H) sweep<ENERGY, M, H>(g, B, I, eh, cnt, xq, pr, lane, lam_v, a_sc, soft_window, fx, fy, fz, ec, el, Bw, lam_e, permw, base)
+#define FELIS_SWEEP(M, H) sweep<ENERGY, M, H>(g, B, I, eh, cnt, xq, pr, lane, lam_v, a_sc, soft_window, fx, fy, fz, ec, el)
     if (half == 0) {
       if (img == 2) FELIS_SWEEP(2, 0);
       else if (img == 1) FELIS_SWEEP(1, 0);
@@ -407,9 +364,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
       }
       cx = -fs * d.x; cy = -fs * d.y; cz = -fs * d.z;      // F_i = fs (r_i - r_j)
       ex = 0.5 * (double)en;
-      if (ENERGY == 2)
-        ex = 0.5 * excl_energy_fp64(g, g.box[w], oa, ob, window_charge_fp64(g, ai, (double)le),
-                                    window_charge_fp64(g, b, (double)le));
     }
   }
   for (int o = 8; o < 64; o <<= 1) {
@@ -450,6 +404,253 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
       atomicAdd((unsigned long long*)&acc[FELIS_E_EXCL],
                 (unsigned long long)to_fixed(ex, kEnergyScale, g.err, kSitePairsE, w));
     }
+  }
+}
+
+// FP64 energies of the real-space terms (felis_nonbonded with FELIS_ENERGY):
+// every pair once, every term in FP64 from the raw (unwrapped) coordinates:
+// the minimum-image distance d - L rint(d (1/L)) and d^2 = (dx^2 + dy^2) +
+// dz^2 without contraction, the cutoff r < r_c on r = sqrt(d^2), the window's
+// charges in FP64, Lorentz-Berthelot parameters from the packed (sigma/2,
+// 2 sqrt(eps)) and the softcore form at lambda_vdw for pairs touching the
+// ligand.
+//
+// One wave per cluster, as in the force sweep, but the FP64 arithmetic (some
+// 200 instructions a pair) is the whole cost, so no lane may idle in it and
+// no pair may be taken twice.  Both clusters of a pair list it: the pair is
+// taken from cluster ci's list when ci < cj and ci + cj is odd or ci > cj and
+// ci + cj is even (each list then gives half of its entries), within a cluster
+// from its lower slot.  The entries kept are queued in LDS; 64 at a time, an
+// FP32 distance with 0.01 A of room (the lists' own margin) drops what lies
+// beyond the cutoff, and what is left is queued in turn and evaluated 64 pairs
+// at a time.
+// 20 windows of 7,540 atoms, 32 M pairs: 2.50 ms as a branch of the force sweep
+// (both sides of every pair, half of the lanes idle, the library's erfc),
+// 0.45 ms from one side with the queue of pairs alone, 0.39 ms with both queues.
+constexpr int kEntQueue = 64 + 64;             // entries: less than a wave's worth kept, one step's pushes
+constexpr int kPairQueue = 64 + 4 * 64;        // pairs, likewise
+
+// 1/x and 1/sqrt(x) in FP64: the hardware estimates (some 2^-26) refined by two
+// Newton steps to about one rounding (x normal and finite)
+__device__ __forceinline__ double rcp_fp64(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ __forceinline__ double rsqrt_fp64(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+
+struct EnergyAtoms {                           // a cluster's atoms (LDS, per wave)
+  float x[kClus], y[kClus], z[kClus];          // raw coordinates
+  float hs[kClus], e2[kClus];                  // packed LJ parameters
+  double q[kClus];                             // the window's charges x KE
+};
+
+// a leg's arrays and constants the pair loop reads, held in registers
+struct EnergyLeg {
+  gptr<float> x, y, z, q, aoff;                  // coordinates of the window; topology
+  gptr<uint8_t> lig;
+  bool has_off;
+  double L[3], iL[3], rc, alpha, sc_alpha, lam_e, lam_v;
+};
+
+__device__ __forceinline__ void pair_energy_fp64(const EnergyLeg& g, const EnergyAtoms& A, int ii, int aj, f32x2 pj,
+                                                 double& ec, double& el) {
+#pragma clang fp contract(off)
+  // every load first: one wait covers them all
+  const float xj = g.x[aj], yj = g.y[aj], zj = g.z[aj], q1 = g.q[aj];
+  const uint8_t lj = g.lig[aj];
+  const float off = g.has_off ? g.aoff[aj] : 0.f;
+  double dx = (double)A.x[ii] - (double)xj, dy = (double)A.y[ii] - (double)yj;
+  double dz = (double)A.z[ii] - (double)zj;
+  dx = dx - g.L[0] * rint(dx * g.iL[0]);
+  dy = dy - g.L[1] * rint(dy * g.iL[1]);
+  dz = dz - g.L[2] * rint(dz * g.iL[2]);
+  const double r2 = (dx * dx + dy * dy) + dz * dz;
+  const double r = sqrt(r2);
+  if (!(r < g.rc)) return;
+  const double qj = (double)q1 * (lj ? g.lam_e : 1.0) + (1.0 - g.lam_e) * (double)off;
+  // erfc(alpha r) by the fit of erfc_coeffs_fp64.h (within 1e-15; alpha r_c <=
+  // 3.5): without the range branches of the library's erfc, which a wave of
+  // distances from 1 to 10 A takes all of
+  const double rinv = rsqrt_fp64(r2);
+  const double xa = g.alpha * r;
+  const double t = rcp_fp64(fma(FELIS_ERFC64_P, xa, 1.0));
+  const double sv = fma(FELIS_ERFC64_A, t, FELIS_ERFC64_B);
+  double pt = felis_erfc64_c[0];
+#pragma unroll
+  for (int k = 1; k < FELIS_ERFC64_NC; ++k) pt = fma(pt, sv, felis_erfc64_c[k]);
+  ec += A.q[ii] * qj * (t * pt * exp(-xa * xa)) * rinv;
+  const float e2i = A.e2[ii];
+  const double eps = 0.25 * (double)fabsf(e2i) * (double)fabsf(pj.y);
+  if (eps == 0.0) return;
+  const double sig = (double)A.hs[ii] + (double)pj.x;
+  const double lam = ((__float_as_uint(e2i) | __float_as_uint(pj.y)) >> 31) ? g.lam_v : 1.0;
+  const double s2 = sig * sig, s6 = s2 * s2 * s2;
+  const double u = s6 * rcp_fp64(g.sc_alpha * (1.0 - lam) * s6 + r2 * r2 * r2);
+  el += lam * 4.0 * eps * (u * u - u);
+}
+
+__device__ __forceinline__ void wave_lds_fence() {     // LDS written by a wave, then read by its other lanes
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+__global__ __launch_bounds__(256) void k_pair_energy(const LegDev* legs, BlockMap map) {
+  const int leg = find_leg(map, blockIdx.x);
+  const LegDev& g = legs[leg];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const long long item = (long long)(blockIdx.x - map.start[leg]) * 4 + wave;
+  if (item >= (long long)g.W * g.nclus) return;
+  const int w = (int)(item / g.nclus);
+  const int c = (int)(item - (long long)w * g.nclus);
+  const BoxW& B = g.box[w];
+  const BoxF Bf = box_f(B);
+  const double lam_e = (double)g.lam[4 * w];
+  const size_t base = (size_t)w * g.n;
+  const gptr<int> permw = as_global(g.perm + (size_t)w * g.npad);
+  EnergyLeg G;
+  G.x = as_global(g.x + base); G.y = as_global(g.y + base); G.z = as_global(g.z + base);
+  G.q = as_global(g.q); G.lig = as_global(g.lig); G.aoff = as_global(g.aoff);
+  G.has_off = g.aoff != nullptr;
+  for (int d = 0; d < 3; ++d) { G.L[d] = B.L[d]; G.iL[d] = B.invL[d]; }
+  G.rc = g.rcd; G.alpha = g.alphad; G.sc_alpha = g.sc_alphad;
+  G.lam_e = lam_e; G.lam_v = (double)g.lam[4 * w + 1];
+  const gptr<f32x4> xq = as_global4(g.xyzq + (size_t)w * g.npad);
+  const gptr<f32x2> pr = as_global2(g.prm + (size_t)w * g.npad);
+  __shared__ EnergyAtoms s_at[4];
+  __shared__ unsigned s_ent[4][kEntQueue];       // partner's slot << 4 | 4-bit mask over the half's atoms
+  __shared__ uint2 s_pair[4][kPairQueue];        // partner's slot << 3 | atom of the cluster; partner's atom index
+  EnergyAtoms& A = s_at[wave];
+  unsigned* eq = s_ent[wave];
+  uint2* pq = s_pair[wave];
+  if (lane < kClus) {
+    const int a = permw[c * kClus + lane];
+    const f32x2 p = pr[c * kClus + lane];
+    A.x[lane] = a >= 0 ? g.x[base + a] : 0.f;
+    A.y[lane] = a >= 0 ? g.y[base + a] : 0.f;
+    A.z[lane] = a >= 0 ? g.z[base + a] : 0.f;
+    A.q[lane] = a >= 0 ? kKE * window_charge_fp64(g, a, lam_e) : 0.0;
+    A.hs[lane] = p.x;
+    A.e2[lane] = p.y;
+  }
+  wave_lds_fence();
+  const float rpre = (float)g.rcd + 0.01f, rpre2 = rpre * rpre;
+  const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  double ec = 0.0, el = 0.0;
+  int ne = 0, np = 0;                            // queued entries and pairs (the same in every lane)
+  auto pairs = [&](int first, int count) {
+    if (lane < count) {
+      const uint2 v = pq[first + lane];
+      pair_energy_fp64(G, A, (int)(v.x & 7u), (int)v.y, pr[v.x >> 3], ec, el);
+    }
+  };
+  for (int half = 0; half < 2; ++half) {
+    const gptr<unsigned> ent = as_global(g.lent + ((size_t)item * 2 + half) * g.cap);
+    const int cnt = g.lcount[2 * item + half];
+    float xi[4], yi[4], zi[4], ext[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const f32x4 a = xq[c * kClus + 4 * half + k];
+      xi[k] = uniform(a.x); yi[k] = uniform(a.y); zi[k] = uniform(a.z);
+      if (k) {                                   // the images nearest the half's first atom
+        xi[k] = fmaf(-Bf.L[0], rintf((xi[k] - xi[0]) * Bf.iL[0]), xi[k]);
+        yi[k] = fmaf(-Bf.L[1], rintf((yi[k] - yi[0]) * Bf.iL[1]), yi[k]);
+        zi[k] = fmaf(-Bf.L[2], rintf((zi[k] - zi[0]) * Bf.iL[2]), zi[k]);
+        if (c * kClus + 4 * half + k < g.n) {
+          ext[0] = fmaxf(ext[0], fabsf(xi[k] - xi[0]));
+          ext[1] = fmaxf(ext[1], fabsf(yi[k] - yi[0]));
+          ext[2] = fmaxf(ext[2], fabsf(zi[k] - zi[0]));
+        }
+      }
+    }
+    // one periodic image per entry, against the half's first atom, is the
+    // nearest for all four when the cutoff and the half's extent fit in L/2
+    const bool shift = rpre + 0.01f + ext[0] < 0.5f * Bf.L[0] && rpre + 0.01f + ext[1] < 0.5f * Bf.L[1] &&
+                       rpre + 0.01f + ext[2] < 0.5f * Bf.L[2];
+    // distances of 64 queued entries
+    auto entries = [&](int first, int count) {
+      const unsigned e = lane < count ? eq[first + lane] : 0u;       // slot 0 with an empty mask
+      const int s = (int)(e >> 4);
+      const f32x4 xj = xq[s];
+      const unsigned aj = (unsigned)permw[s];
+      float jx = xj.x, jy = xj.y, jz = xj.z;
+      if (shift) {
+        jx = fmaf(-Bf.L[0], rintf((jx - xi[0]) * Bf.iL[0]), jx);
+        jy = fmaf(-Bf.L[1], rintf((jy - yi[0]) * Bf.iL[1]), jy);
+        jz = fmaf(-Bf.L[2], rintf((jz - zi[0]) * Bf.iL[2]), jz);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float dx = jx - xi[k], dy = jy - yi[k], dz = jz - zi[k];
+        if (!shift) {
+          dx = fmaf(-Bf.L[0], rintf(dx * Bf.iL[0]), dx);
+          dy = fmaf(-Bf.L[1], rintf(dy * Bf.iL[1]), dy);
+          dz = fmaf(-Bf.L[2], rintf(dz * Bf.iL[2]), dz);
+        }
+        const bool in = ((e >> k) & 1u) && fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < rpre2;
+        const unsigned long long m = __ballot(in);
+        if (in) pq[np + __popcll(m & lt)] = make_uint2((unsigned)s << 3 | (unsigned)(4 * half + k), aj);
+        np += __popcll(m);
+      }
+      wave_lds_fence();
+      while (np >= 64) {
+        np -= 64;
+        pairs(np, 64);
+      }
+      wave_lds_fence();
+    };
+    for (int it = 0; it < cnt; it += 64) {
+      const unsigned v = it + lane < cnt ? ent[it + lane] : 0u;
+      const int s = (int)(v >> 8), cj = s >> 3;
+      unsigned m = v & 0xFu;
+      if (cj == c) {
+        const int below = min(max((s & 7) - 4 * half, 0), 4);          // atoms of the half with a lower slot
+        m &= (1u << below) - 1u;
+      } else if ((((cj + c) & 1) != 0) != (cj > c)) {
+        m = 0u;
+      }
+      const unsigned long long b = __ballot(m != 0u);
+      if (m) eq[ne + __popcll(b & lt)] = (unsigned)s << 4 | m;
+      ne += __popcll(b);
+      wave_lds_fence();
+      if (ne >= 64) {
+        ne -= 64;
+        entries(ne, 64);
+      }
+    }
+    entries(0, ne);                              // the queue holds one half's entries: empty it
+    ne = 0;
+  }
+  pairs(0, np);
+  // excluded pairs, each from its lower atom: lane = ii + 8 k takes the k-th
+  // exclusion of atom ii
+  double ex = 0.0;
+  const int ai = permw[c * kClus + (lane & 7)];
+  if (ai >= 0) {
+    const int e0 = g.excl_ptr[ai], ne = min(g.excl_ptr[ai + 1] - e0, kMaxExcl);
+    const int k = lane >> 3;
+    if (k < ne) {
+      const int b = g.excl_idx[e0 + k];
+      if (b > ai)
+        ex = excl_energy_fp64(g, B, base + ai, base + b, window_charge_fp64(g, ai, lam_e),
+                              window_charge_fp64(g, b, lam_e));
+    }
+  }
+  ec = wave_sum(ec);
+  el = wave_sum(el);
+  ex = wave_sum(ex);
+  if (lane == 0) {
+    long long* acc = g.eacc + (size_t)w * FELIS_NE;
+    atomicAdd((unsigned long long*)&acc[FELIS_E_COUL_REAL],
+              (unsigned long long)to_fixed(ec, kEnergyScale, g.err, kSitePairsE, w));
+    atomicAdd((unsigned long long*)&acc[FELIS_E_LJ],
+              (unsigned long long)to_fixed(el, kEnergyScale, g.err, kSitePairsE, w));
+    atomicAdd((unsigned long long*)&acc[FELIS_E_EXCL],
+              (unsigned long long)to_fixed(ex, kEnergyScale, g.err, kSitePairsE, w));
   }
 }
 
@@ -652,9 +853,9 @@ void launch_pairs(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int 
   const int nb = make_map(m, nl, [&](int i) { return blocks_for((long long)h[i].W * h[i].nclus, 4); });
   if (!nb) return;
   const int st = step ? 1 : 0;
-  if (energy == 2) hipLaunchKernelGGL(k_pairs<2>, dim3(nb), dim3(256), 0, s, d, m, 0);
-  else if (energy == 1) hipLaunchKernelGGL(k_pairs<1>, dim3(nb), dim3(256), 0, s, d, m, 0);
+  if (energy == 1) hipLaunchKernelGGL(k_pairs<1>, dim3(nb), dim3(256), 0, s, d, m, 0);
   else hipLaunchKernelGGL(k_pairs<0>, dim3(nb), dim3(256), 0, s, d, m, st);
+  if (energy == 2) hipLaunchKernelGGL(k_pair_energy, dim3(nb), dim3(256), 0, s, d, m);
 }
 
 void launch_corrections(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool energy) {

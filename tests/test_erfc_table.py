@@ -55,3 +55,19 @@ def test_every_step_rounded_to_fp32():
     rel = e.astype(np.float64) / erfc(x.astype(np.float64)) - 1.0
     # a few FP32 ulps: the rounding of t and of x^2 dominates near x = 3.5
     assert np.max(np.abs(rel)) <= 1.5e-6, np.max(np.abs(rel))
+
+
+HEADER64 = CSRC / 'erfc_coeffs_fp64.h'
+
+
+def test_fp64_table_is_what_its_generator_writes_and_matches_erfc():
+    out = subprocess.run([sys.executable, str(CSRC / 'gen_erfc_coeffs_fp64.py')],
+                         capture_output=True, text=True, check=True, timeout=120).stdout
+    assert out == HEADER64.read_text()
+    a, b, p = (float(re.search(r'FELIS_ERFC64_%s (\S+)\n' % k, out).group(1)) for k in 'ABP')
+    c = [float(v) for v in re.findall(r'^\s+(-?[0-9.]+e[+-][0-9]+)', out, re.M)]
+    x = np.linspace(0.0, 3.5, 400_001)
+    t = 1.0 / (1.0 + p * x)
+    rel = t * np.polyval(c, a * t + b) * np.exp(-x * x) / erfc(x) - 1.0
+    # the rounding of x^2 (up to 12.25) alone gives 12.25 x 2^-53 = 1.4e-15
+    assert np.max(np.abs(rel)) <= 5e-15, np.max(np.abs(rel))
