@@ -20,7 +20,7 @@ namespace {
 
 struct Layout {
   size_t lam, lamS, rstate, free_atoms, lig_idx, aw_idx, fd, xr, yr, zr, flag, nbuild, maxdisp, wmax, hcell, box, ubox, rbforce, skin_used, bptr, bnb, bid, tptr, tid, mol_ptr, mol_atoms, baro, boxb, xb, yb, zb, molr, perm, cellcode, cellstart, cursor, xyzq, prm, bblo,
-      bbhi, gsten, lcount, lent, frx, fry, frz, grid64, cgrid, tw[3], bmod[3], eacc, uacc, upart, lpart, ucst, total;
+      bbhi, gsten, lcount, lent, frx, fry, frz, grid64, cgrid, uflag, usph, uphi, tw[3], bmod[3], eacc, uacc, upart, lpart, ucst, total;
 };
 
 struct Plan {
@@ -216,6 +216,9 @@ int make_plan(felis_ctx* c, const felis_leg* L, Plan& P) {
   y.frx = put(W * n * 8); y.fry = put(W * n * 8); y.frz = put(W * n * 8);
   y.grid64 = put(2 * (size_t)h.npair * h.Ktot * 8);
   y.cgrid = put((size_t)h.npair * h.Ktot * 8);
+  y.usph = put(2 * (size_t)h.npair * 16);
+  y.uphi = put(2 * (size_t)h.npair * UknLines(h.K).size * 4);
+  y.uflag = put((size_t)h.npair * h.K[2] * (ukn_chunks(h.K[1]) + 1) * 4);
   for (int d = 0; d < 3; ++d) { y.tw[d] = put(h.K[d] * 8); y.bmod[d] = put(h.K[d] * 4); }
   y.eacc = put(W * FELIS_NE * 8);
   y.uacc = put(2 * (size_t)h.npair * (3 + kMaxLamV) * 8);
@@ -322,6 +325,9 @@ LegDev make_dev(const felis_ctx* c, const felis_leg* L, const Plan& p, const Met
   g.frx = (long long*)(w + y.frx); g.fry = (long long*)(w + y.fry); g.frz = (long long*)(w + y.frz);
   g.grid64 = (long long*)(w + y.grid64);
   g.cgrid = (float2*)(w + y.cgrid);
+  g.usph = (float4*)(w + y.usph);
+  g.uphi = (float*)(w + y.uphi);
+  g.uflag = (int*)(w + y.uflag);
   for (int d = 0; d < 3; ++d) { g.tw[d] = (float2*)(w + y.tw[d]); g.bmod[d] = (float*)(w + y.bmod[d]); }
   g.eacc = (long long*)(w + y.eacc);
   g.uacc = (long long*)(w + y.uacc);
@@ -968,9 +974,8 @@ int felis_ukn(felis_ctx* c, felis_leg* leg, const double* lambdas, int K, const 
   make_plan(c, leg, p);
   char* w = (char*)leg->work;
   mark(c, FELIS_PROF_UKN, false);
-  rc = launch_ukn(c->stream, c->d_legs, hs[0], leg->sc_alpha, lambdas, K, fx, fy, fz, frame_stride, n_frames,
-                  frame_box, leg->pressure_bar * kBar, beta, u, u_stride, (long long*)(w + p.lay.uacc),
-                  (double*)(w + p.lay.ucst));
+  rc = launch_ukn(c->stream, c->side, c->ev_fork, c->ev_join, c->d_legs, hs[0], leg->sc_alpha, lambdas, K, fx, fy, fz, frame_stride, n_frames,
+                  frame_box, leg->pressure_bar * kBar, beta, u, u_stride, (double*)(w + p.lay.ucst));
   mark(c, FELIS_PROF_UKN, true);
   if (rc) return fail(c, rc, "u_kn: more than 128 states, 64 distinct lambda_vdw or 256 ligand atoms");
   return launched(c);

@@ -158,6 +158,10 @@ struct LegDev {
                                         // atoms 4-7 (slot << 8 | 4-bit mask over the half's atoms)
   long long *frx, *fry, *frz;           // [W][n] reciprocal-space forces of the current MD step
   long long* grid64;                    // [2 npair][Ktot] u_kn ligand charge grids, fixed point
+  float* uphi;                          // [2 npair][UknLines size] u_kn: each frame's ligand potential
+  float4* usph;                         // [2 npair] u_kn: the ligand's bounding sphere per frame (centre, radius)
+  int* uflag;                           // [npair][K2 (chunks + 1)] u_kn: 16-row chunks of each z plane, then the
+                                        // planes themselves, that the frame's charges touch
   float2* cgrid;                        // [npair][Ktot] complex grids
   float2* tw[3];                        // [K] exp(-2 pi i k / K) per axis
   float* bmod[3];                       // [K] B-spline moduli factor per axis
@@ -168,6 +172,26 @@ struct LegDev {
   int* err;                             // context error word
   int* need;                            // context: largest list length seen
   int leg_index;                        // position of this leg in the launched batch
+};
+
+// u_kn grids: 16-row chunks per z plane, and the flags of grid p
+__host__ __device__ inline int ukn_chunks(int Ky) { return (Ky + 15) / 16; }
+__device__ __forceinline__ int* ukn_flags(const LegDev& g, int p) {
+  return g.uflag + (size_t)p * g.K[2] * (ukn_chunks(g.K[1]) + 1);
+}
+
+// A u_kn frame's potential for the gather, in 128-byte lines of 4 x 4 x 2
+// points (x, y, z): an atom's 4 x 4 x 4 points lie in (1.75)^2 2.5 = 7.7 lines
+// on average, against some 19 of a row-major complex grid.
+struct UknLines {
+  int nx, ny, nz;                       // lines per axis
+  int size;                             // floats
+  __host__ __device__ explicit UknLines(const int* K)
+      : nx((K[0] + 3) / 4), ny((K[1] + 3) / 4), nz((K[2] + 1) / 2), size(nx * ny * nz * 32) {}
+  // a point's offset is the sum of its axes' parts
+  __device__ __forceinline__ int x(int v) const { return (v >> 2) * 32 + (v & 3); }
+  __device__ __forceinline__ int y(int v) const { return (v >> 2) * nx * 32 + (v & 3) * 4; }
+  __device__ __forceinline__ int z(int v) const { return (v >> 1) * nx * ny * 32 + (v & 1) * 16; }
 };
 
 // Maps a flat block index to (leg, block within leg) for batched launches.
@@ -371,16 +395,15 @@ void launch_integrate(hipStream_t s, const LegDev* d, const LegHost* h, int nl,
                       float temperature, float gamma);
 void launch_zero_energy(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int c0, int c1);
 void launch_finish_energy(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int c0, int c1);
-void launch_fill_i64(hipStream_t s, long long* p, size_t n);
 // ukn_mode: 0 the MD grids; u_kn int64 grids of 1 two frames per complex grid
 // or 2 one frame per grid (boxes from ubox)
 void launch_pme_fft(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int ukn_mode);
 void launch_hrex(hipStream_t s, const LegDev* d, const LegHost& h, const double* u, long long u_stride,
                  long long attempt, unsigned long long seed, int* accepted);
-int launch_ukn(hipStream_t s, const LegDev* d, const LegHost& h, double sc_alpha, const double* lambdas,
+int launch_ukn(hipStream_t s, hipStream_t side, hipEvent_t ev_fork, hipEvent_t ev_join, const LegDev* d, const LegHost& h, double sc_alpha, const double* lambdas,
                int K, const float* fx, const float* fy, const float* fz, long long frame_stride,
                long long n_frames, const double* frame_box, double pressure, double beta, double* u,
-               long long u_stride, long long* uacc, double* cst);
+               long long u_stride, double* cst);
 // barostat: proposal, box change and molecule move of the due windows; the
 // energy before the move; Metropolis test, restore of rejected moves
 void launch_baro_propose(hipStream_t s, const LegDev* d, const LegHost* h, int nl, const BaroArgs& A);

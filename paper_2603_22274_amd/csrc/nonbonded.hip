@@ -831,11 +831,6 @@ __global__ void k_efinish(const LegDev* legs, BlockMap map, int c0, int c1) {
   e[FELIS_E_TOTAL] = t;
 }
 
-__global__ void k_fill_i64(long long* p, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
 inline int blocks_for(long long items, int per) { return (int)((items + per - 1) / per); }
 
 }  // namespace
@@ -885,10 +880,6 @@ void launch_finish_energy(hipStream_t s, const LegDev* d, const LegHost* h, int 
   BlockMap m;
   const int nb = make_map(m, nl, [&](int i) { return blocks_for(h[i].W, 64); });
   if (nb) hipLaunchKernelGGL(k_efinish, dim3(nb), dim3(64), 0, s, d, m, c0, c1);
-}
-
-void launch_fill_i64(hipStream_t s, long long* p, size_t n) {
-  if (n) hipLaunchKernelGGL(k_fill_i64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n);
 }
 
 }  // namespace felis

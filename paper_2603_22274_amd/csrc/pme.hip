@@ -164,8 +164,10 @@ __device__ __forceinline__ void stage_first_global(const float2* __restrict__ cg
     float2 v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
+      // (an unconditional load, so that all R are in flight together)
       const long long off = offs(j + r * nR, b);
-      const float2 c = off >= 0 ? cg[off] : make_float2(0.f, 0.f);
+      const float2 g = cg[off < 0 ? 0 : off];
+      const float2 c = off < 0 ? make_float2(0.f, 0.f) : g;
       v[r] = CONJ ? conj2(c) : c;
     }
     dft<R>(v);
@@ -232,10 +234,17 @@ __device__ __forceinline__ float2* fft_lines(float2* src, float2* dst, int n, co
   return src;
 }
 
-// MODE: 0 forward, 1 inverse, 2 forward from the int64 grids (x axis),
-//       3 forward * G * inverse (z axis)
-template <int AXIS, int MODE, int LINES>
+// FORM: 0 forward, 1 inverse, 2 forward from the int64 grids (x axis),
+//       3 forward * G * inverse (z axis); of the u_kn grids, whose charges are
+//       a few dozen ligand atoms, 4 forward (y axis) and 5 as 3: only the rows
+//       that the charges touch (uflag) are read and transformed, what was not
+//       touched counts as zero.  2 skips untouched chunks likewise.  6 as 1 on
+//       the x axis, but the two frames' potentials go to uphi, each by itself
+//       in lines of 4 x 4 x 2 points for the gather.
+template <int AXIS, int FORM, int LINES>
 __global__ __launch_bounds__(256) void k_fft(const LegDev* legs, BlockMap map, int ukn) {
+  constexpr int MODE = FORM == 4 ? 0 : (FORM == 5 ? 3 : (FORM == 6 ? 1 : FORM));
+  static_assert(FORM != 2 || LINES == 16, "a workgroup of the x pass transforms one flagged chunk");
   const int leg = find_leg(map, blockIdx.x);
   const LegDev& g = legs[leg];
   const int Kx = g.K[0], Ky = g.K[1], Kz = g.K[2];
@@ -249,6 +258,18 @@ __global__ __launch_bounds__(256) void k_fft(const LegDev* legs, BlockMap map, i
   const int rem = bl - p * outer * nch;
   const int o = rem / nch, ch = rem - (rem / nch) * nch;
   if (p >= g.npair) return;
+  // rows (y axis: 16-row chunks) or planes (z axis) that hold charge, a bit each
+  unsigned long long touched[2] = {~0ull, ~0ull};
+  if (FORM == 2) {
+    if (!ukn_flags(g, p)[o * nch + ch]) return;  // uniform over the block
+  } else if (FORM == 4 || FORM == 5) {
+    const int nk = ukn_chunks(Ky), lane = threadIdx.x & 63;
+    const int* fl = ukn_flags(g, p) + (FORM == 4 ? o * nk : Kz * nk);
+    const int cnt = FORM == 4 ? nk : Kz;
+    touched[0] = __ballot(lane < cnt && fl[min(lane, cnt - 1)]);
+    touched[1] = __ballot(lane + 64 < cnt && fl[min(lane + 64, cnt - 1)]);
+    if (FORM == 4 && !touched[0]) return;        // an empty plane (at most 8 chunks)
+  }
   extern __shared__ float2 smem[];               // two buffers of n * LINES, then n twiddles
   float2* bufA = smem;
   float2* bufB = smem + (size_t)n * LINES;
@@ -264,17 +285,26 @@ __global__ __launch_bounds__(256) void k_fft(const LegDev* legs, BlockMap map, i
     if (AXIS == 1) return (long long)o * KxKy + (long long)e * Kx + li;
     return (long long)e * KxKy + (long long)o * Kx + li;
   };
+  const unsigned tw32[4] = {(unsigned)touched[0], (unsigned)(touched[0] >> 32), (unsigned)touched[1],
+                            (unsigned)(touched[1] >> 32)};
+  // where the first stage reads an element (< 0: it is zero)
+  auto offs_in = [&](int e, int b) -> long long {
+    if (FORM == 4 && !((tw32[0] >> (e >> 4)) & 1u)) return -1;
+    if (FORM == 5 && !((((e & 64) ? ((e & 32) ? tw32[3] : tw32[2]) : ((e & 32) ? tw32[1] : tw32[0])) >> (e & 31)) & 1u))
+      return -1;
+    return offs(e, b);
+  };
   float2* res;
   if (AXIS != 0 && MODE != 2) {
     // the first stage reads the grid itself (no staging pass through LDS)
     constexpr bool CJ = MODE == 1;
     switch (g.rad[AXIS][0]) {
-      case 2: stage_first_global<2, LINES, CJ>(cg, offs, bufA, n); break;
-      case 3: stage_first_global<3, LINES, CJ>(cg, offs, bufA, n); break;
-      case 4: stage_first_global<4, LINES, CJ>(cg, offs, bufA, n); break;
-      case 8: stage_first_global<8, LINES, CJ>(cg, offs, bufA, n); break;
-      case 12: stage_first_global<12, LINES, CJ>(cg, offs, bufA, n); break;
-      default: stage_first_global<5, LINES, CJ>(cg, offs, bufA, n); break;
+      case 2: stage_first_global<2, LINES, CJ>(cg, offs_in, bufA, n); break;
+      case 3: stage_first_global<3, LINES, CJ>(cg, offs_in, bufA, n); break;
+      case 4: stage_first_global<4, LINES, CJ>(cg, offs_in, bufA, n); break;
+      case 8: stage_first_global<8, LINES, CJ>(cg, offs_in, bufA, n); break;
+      case 12: stage_first_global<12, LINES, CJ>(cg, offs_in, bufA, n); break;
+      default: stage_first_global<5, LINES, CJ>(cg, offs_in, bufA, n); break;
     }
     __syncthreads();
     const int nrad = g.nrad[AXIS];
@@ -360,6 +390,23 @@ __global__ __launch_bounds__(256) void k_fft(const LegDev* legs, BlockMap map, i
       return;
     }
     res = fft_lines<LINES>(res, other, n, g.rad[AXIS], nrad, tw);
+  }
+  if (FORM == 6) {
+    // 4 x 4 points (x, y) of the plane are half a line: 16 consecutive threads
+    const UknLines l(g.K);
+    float* re = g.uphi + (size_t)(2 * p) * l.size;
+    float* im = re + l.size;
+    const int nq = l.nx * (LINES / 4);
+    for (int idx = threadIdx.x; idx < nq * 16; idx += blockDim.x) {
+      const int q = idx >> 4, qy = q / l.nx, e = 4 * (q - qy * l.nx) + (idx & 3), b = 4 * qy + ((idx >> 2) & 3);
+      const int y = ch * LINES + b;
+      if (e >= n || y >= inner) continue;
+      const float2 v = conj2(res[e * LINES + b]);
+      const int at = l.x(e) + l.y(y) + l.z(o);
+      re[at] = v.x;
+      if (ukn == 1) im[at] = v.y;
+    }
+    return;
   }
   for (int idx = threadIdx.x; idx < n * LINES; idx += blockDim.x) {
     int e, b;
@@ -924,14 +971,14 @@ void fft_launch(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int uk
 constexpr long long kFftWideBlocks = 4096;
 
 template <int AXIS, int MODE>
-void fft_pass(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int ukn, bool allow_wide) {
+void fft_pass(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int ukn) {
   long long wide = 0;
   for (int i = 0; i < nl; ++i) {
     const int inner = (AXIS == 0) ? h[i].K[1] : h[i].K[0];
     const int outer = (AXIS == 2) ? h[i].K[1] : h[i].K[2];
     wide += (long long)h[i].npair * outer * ((inner + 31) / 32);
   }
-  if (allow_wide && wide >= kFftWideBlocks) fft_launch<AXIS, MODE, 32>(s, d, h, nl, ukn);
+  if (wide >= kFftWideBlocks) fft_launch<AXIS, MODE, 32>(s, d, h, nl, ukn);
   else fft_launch<AXIS, MODE, 16>(s, d, h, nl, ukn);
 }
 
@@ -961,7 +1008,6 @@ size_t plane_lds_limit() {
 }
 
 void launch_pme_fft(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int ukn_mode) {
-  const bool wide = ukn_mode == 0;              // MD and force passes; u_kn keeps 16 lines
   const bool from_int64 = ukn_mode != 0;
   int plane = 0, kxy = 0;
   for (int i = 0; i < nl; ++i) {
@@ -973,16 +1019,23 @@ void launch_pme_fft(hipStream_t s, const LegDev* d, const LegHost* h, int nl, in
     BlockMap m;
     const int nb = make_map(m, nl, [&](int i) { return h[i].npair * h[i].K[2]; });
     if (nb) hipLaunchKernelGGL(k_fft_xy<false>, dim3(nb), dim3(kXYThreads), lds, s, d, m);
-    fft_pass<2, 3>(s, d, h, nl, ukn_mode, wide);
+    fft_pass<2, 3>(s, d, h, nl, 0);
     if (nb) hipLaunchKernelGGL(k_fft_xy<true>, dim3(nb), dim3(kXYThreads), lds, s, d, m);
     return;
   }
-  if (from_int64) fft_pass<0, 2>(s, d, h, nl, 0, wide);
-  else fft_pass<0, 0>(s, d, h, nl, 0, wide);
-  fft_pass<1, 0>(s, d, h, nl, 0, wide);
-  fft_pass<2, 3>(s, d, h, nl, ukn_mode, wide);
-  fft_pass<1, 1>(s, d, h, nl, 0, wide);
-  fft_pass<0, 1>(s, d, h, nl, 0, wide);
+  if (from_int64) {                             // (16 lines per workgroup, as the flags count rows)
+    fft_launch<0, 2, 16>(s, d, h, nl, 0);
+    fft_launch<1, 4, 16>(s, d, h, nl, 0);
+    fft_launch<2, 5, 16>(s, d, h, nl, ukn_mode);
+    fft_launch<1, 1, 16>(s, d, h, nl, 0);
+    fft_launch<0, 6, 16>(s, d, h, nl, ukn_mode);
+    return;
+  }
+  fft_pass<0, 0>(s, d, h, nl, 0);
+  fft_pass<1, 0>(s, d, h, nl, 0);
+  fft_pass<2, 3>(s, d, h, nl, 0);
+  fft_pass<1, 1>(s, d, h, nl, 0);
+  fft_pass<0, 1>(s, d, h, nl, 0);
 }
 
 void launch_pme(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool energy, bool step_forces) {
