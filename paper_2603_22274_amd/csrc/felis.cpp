@@ -19,7 +19,7 @@ using namespace felis;
 namespace {
 
 struct Layout {
-  size_t lam, lamS, rstate, free_atoms, lig_idx, aw_idx, fd, xr, yr, zr, flag, nbuild, maxdisp, wmax, hcell, box, ubox, rbforce, skin_used, bptr, bnb, bid, tptr, tid, mol_ptr, mol_atoms, baro, boxb, xb, yb, zb, molr, perm, cellcode, cellstart, cursor, xyzq, prm, bblo,
+  size_t lam, lamS, rstate, free_atoms, lig_idx, aw_idx, fd, xr, yr, zr, flag, nbuild, maxdisp, wmax, hcell, box, ubox, rbforce, skin_used, bptr, bnb, bid, tptr, tid, batoms, mol_ptr, mol_atoms, baro, boxb, xb, yb, zb, molr, perm, cellcode, cellstart, cursor, xyzq, prm, bblo,
       bbhi, gsten, lcount, lent, frx, fry, frz, grid64, cgrid, uflag, usph, uphi, tw[3], bmod[3], eacc, uacc, upart, lpart, ucst, total;
 };
 
@@ -33,6 +33,7 @@ struct Plan {
 struct Meta {          // facts read from the topology at felis_leg_init
   int nfree, nlig;
   int naw;             // alchemical-water atoms
+  int nba;             // atoms with bonded terms
   int nmol;            // molecules (legs with a barostat; 0 otherwise)
   size_t work_bytes;
 };
@@ -187,6 +188,7 @@ int make_plan(felis_ctx* c, const felis_leg* L, Plan& P) {
   y.bid = put(2 * (size_t)std::max(h.nbonds, 1) * 4);
   y.tptr = put((n + 1) * 4);                      // per-atom torsion table (filled at set-up)
   y.tid = put(4 * (size_t)std::max(h.ntors, 1) * 4);
+  y.batoms = put(n * 4);                          // atoms with bonded terms (filled at set-up)
   {
     // barostat: molecule table, per-window state, positions before a move
     const bool npt = L->pressure_bar > 0;
@@ -302,6 +304,8 @@ LegDev make_dev(const felis_ctx* c, const felis_leg* L, const Plan& p, const Met
   g.tors = L->torsion_ijkl; g.tors_k = L->torsion_k; g.tors_n = L->torsion_n; g.tors_phase = L->torsion_phase;
   g.tptr = (const int*)(w + y.tptr);
   g.tid = (const int*)(w + y.tid);
+  g.batoms = (const int*)(w + y.batoms);
+  g.nba = m.nba;
   g.nmol = m.nmol;
   if (m.nmol) {
     g.mol_ptr = (const int*)(w + y.mol_ptr);
@@ -355,6 +359,7 @@ int prepare(felis_ctx* c, const felis_leg* legs, int n_legs, std::vector<LegHost
     p.h.nfree = it->second.nfree;
     p.h.nlig = it->second.nlig;
     p.h.naw = it->second.naw;
+    p.h.nba = it->second.nba;
     p.h.nmol = it->second.nmol;
     hs[i] = p.h;
     devs[i] = make_dev(c, &legs[i], p, it->second, i);
@@ -600,6 +605,7 @@ int felis_leg_init(felis_ctx* c, felis_leg* L) {
   m.nfree = (int)freeat.size();
   m.nlig = (int)ligi.size();
   m.naw = 0;
+  m.nba = 0;
   if (L->alch_offset) {
     // alchemical-water atoms (nonzero offset, never ligand atoms) and their
     // two exclusion partners each (the other atoms of the rigid water)
@@ -631,14 +637,18 @@ int felis_leg_init(felis_ctx* c, felis_leg* L) {
   std::vector<int> bij(2 * (size_t)h.nbonds);
   if (h.nbonds && hipMemcpy(bij.data(), L->bond_ij, bij.size() * 4, hipMemcpyDeviceToHost) != hipSuccess)
     return fail(c, FELIS_E_DEVICE, "bond copy failed");
+  std::vector<char> bonded(h.n, 0);     // atoms with bonded terms
+  if (h.has_rest)
+    for (int t = 0; t < 6; ++t) bonded[L->restraint_atoms[t]] = 1;
   {
-    // per-atom bond table for the integrator: for atom a, its partners and
-    // bond indices in bond order
+    // per-atom bond table for the step's bonded forces: for atom a, its
+    // partners and bond indices in bond order
     std::vector<int> ptr(h.n + 1, 0), nb(std::max(2 * h.nbonds, 2)), id(std::max(2 * h.nbonds, 2));
     for (int k = 0; k < h.nbonds; ++k) {
       const int a = bij[2 * k], b = bij[2 * k + 1];
       if (a < 0 || b < 0 || a >= h.n || b >= h.n) return fail(c, FELIS_E_INVAL, "bond atom out of range");
       ++ptr[a + 1]; ++ptr[b + 1];
+      bonded[a] = bonded[b] = 1;
     }
     for (int a = 0; a < h.n; ++a) ptr[a + 1] += ptr[a];
     std::vector<int> fill(ptr.begin(), ptr.end() - 1);
@@ -653,7 +663,7 @@ int felis_leg_init(felis_ctx* c, felis_leg* L) {
     if (!ok) return fail(c, FELIS_E_DEVICE, "bond table");
   }
   {
-    // per-atom torsion table for the integrator: for atom a, entries 4 t + s
+    // per-atom torsion table for the same: for atom a, entries 4 t + s
     // (torsion t, a is its s-th atom) in torsion order
     std::vector<int> tq(4 * (size_t)h.ntors);
     if (h.ntors && hipMemcpy(tq.data(), L->torsion_ijkl, tq.size() * 4, hipMemcpyDeviceToHost) != hipSuccess)
@@ -662,6 +672,7 @@ int felis_leg_init(felis_ctx* c, felis_leg* L) {
     for (size_t e = 0; e < tq.size(); ++e) {
       if (tq[e] < 0 || tq[e] >= h.n) return fail(c, FELIS_E_INVAL, "torsion atom out of range");
       ++ptr[tq[e] + 1];
+      bonded[tq[e]] = 1;
     }
     for (int a = 0; a < h.n; ++a) ptr[a + 1] += ptr[a];
     std::vector<int> fill(ptr.begin(), ptr.end() - 1);
@@ -669,6 +680,14 @@ int felis_leg_init(felis_ctx* c, felis_leg* L) {
     ok &= hipMemcpy(w + y.tptr, ptr.data(), ptr.size() * 4, hipMemcpyHostToDevice) == hipSuccess;
     ok &= hipMemcpy(w + y.tid, id.data(), id.size() * 4, hipMemcpyHostToDevice) == hipSuccess;
     if (!ok) return fail(c, FELIS_E_DEVICE, "torsion table");
+  }
+  {
+    std::vector<int> list;
+    for (int a = 0; a < h.n; ++a)
+      if (bonded[a]) list.push_back(a);
+    m.nba = (int)list.size();
+    if (m.nba && hipMemcpy(w + y.batoms, list.data(), list.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
+      return fail(c, FELIS_E_DEVICE, "bonded atom list");
   }
   if (L->pressure_bar > 0) {
     // molecules: connected components of the bonds with each rigid water's
@@ -856,20 +875,20 @@ int felis_step(felis_ctx* c, felis_leg* legs, int n_legs, int n_steps, double dt
     launch_check(c->stream, c->d_legs, hs.data(), n_legs, 0, s > 0 && !baro);
     launch_sort_pack(c->stream, c->d_legs, hs.data(), n_legs);
     // reciprocal space needs only the cell sort and the packed coordinates
-    // and parameters: it runs on the side stream beside the list build, the
-    // pair kernel and the bonded terms, and stores its forces apart (frx..)
+    // and parameters: it runs on the side stream beside the list build and the
+    // pair kernel, and stores its forces apart (frx..), with the bonded ones
     (void)hipEventRecord(c->ev_fork, c->stream);
     (void)hipStreamWaitEvent(c->side, c->ev_fork, 0);
     mark(c, FELIS_PROF_PME, false, c->side);
     launch_pme(c->side, c->d_legs, hs.data(), n_legs, false, true);
     mark(c, FELIS_PROF_PME, true, c->side);
+    launch_bonded_step(c->side, c->d_legs, hs.data(), n_legs);
     (void)hipEventRecord(c->ev_join, c->side);
     launch_lists(c->stream, c->d_legs, hs.data(), n_legs);
     mark(c, FELIS_PROF_NLIST, true);       // the build stage also packs the sorted coordinates
     mark(c, FELIS_PROF_PAIRS, false);
     launch_pairs(c->stream, c->d_legs, hs.data(), n_legs, 0, true);
     mark(c, FELIS_PROF_PAIRS, true);
-    // bonded and restraint forces are summed by the integrator itself
     (void)hipStreamWaitEvent(c->stream, c->ev_join, 0);
     mark(c, FELIS_PROF_INTEGRATE, false);
     launch_integrate(c->stream, c->d_legs, hs.data(), n_legs, step.data(), seed.data(), (float)dt,

@@ -107,6 +107,8 @@ struct LegDev {
   const float *tors_k, *tors_phase;     // [ntors]
   const int* tors_n;                    // [ntors]
   const int *tptr, *tid;                // per-atom torsions: CSR [n + 1] over 4 t + (the atom's place in t)
+  const int* batoms;                    // [nba] atoms with a bond, a torsion or an anchor
+  int nba;
   const float* aoff;                    // [n] alchemical-water charge offsets (NULL: none)
   int naw;                              // alchemical-water atoms (nonzero offset)
   int* aw_idx;                          // [naw] those atoms, then their two exclusion partners each [2 naw]
@@ -156,7 +158,7 @@ struct LegDev {
   int* lcount;                          // [W][nclus][2] entries per half-cluster list
   unsigned* lent;                       // [W][nclus][2][cap]: list of the cluster's atoms 0-3 and of
                                         // atoms 4-7 (slot << 8 | 4-bit mask over the half's atoms)
-  long long *frx, *fry, *frz;           // [W][n] reciprocal-space forces of the current MD step
+  long long *frx, *fry, *frz;           // [W][n] reciprocal-space and bonded forces of the current MD step
   long long* grid64;                    // [2 npair][Ktot] u_kn ligand charge grids, fixed point
   float* uphi;                          // [2 npair][UknLines size] u_kn: each frame's ligand potential
   float4* usph;                         // [2 npair] u_kn: the ligand's bounding sphere per frame (centre, radius)
@@ -356,7 +358,7 @@ inline int make_map(BlockMap& m, int n_legs, F blocks_of) {
 
 // Host-side mirror of the sizes each launcher needs.
 struct LegHost {
-  int n, W, npad, nclus, cap, nexcl, nbonds, nwat, nfree, nlig, K[3], Ktot, npair, ncell, ntors, naw;
+  int n, W, npad, nclus, cap, nexcl, nbonds, nwat, nfree, nlig, K[3], Ktot, npair, ncell, ntors, naw, nba;
   int has_rest;
   int nmol;                             // > 0 only for legs with a barostat
 };
@@ -390,6 +392,8 @@ void launch_bonded(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int
 // step_forces: the gather stores each atom's force in frx/fry/frz (read by the
 // integrator) instead of adding it to fx/fy/fz
 void launch_pme(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool energy, bool step_forces = false);
+// the step's bonded forces, added to frx/fry/frz (after the gather has stored there)
+void launch_bonded_step(hipStream_t s, const LegDev* d, const LegHost* h, int nl);
 void launch_integrate(hipStream_t s, const LegDev* d, const LegHost* h, int nl,
                       const long long* step, const unsigned long long* seed, float dt,
                       float temperature, float gamma);

@@ -84,7 +84,7 @@ __device__ __attribute__((noinline)) v3 torsion_share(const LegDev& g, int w, in
 // its own, from the per-atom bond table, in bond order), its lambda_vdw-scaled
 // rotatable torsions (per-atom torsion table) and, for a Boresch
 // anchor, its share of the lambda_r-scaled restraint -- the forces of
-// k_bonded, computed where they are used instead of added by atomics.
+// k_bonded, without atomics.
 __device__ __forceinline__ v3 bonded_force(const LegDev& g, int w, int a) {
   v3 F = mk(0.f, 0.f, 0.f);
   const int k0 = g.bptr[a], k1 = g.bptr[a + 1];
@@ -117,19 +117,47 @@ __device__ __forceinline__ v3 bonded_force(const LegDev& g, int w, int a) {
   return F;
 }
 
+// items: window x bonded atom (any atom with a bond, a torsion or an anchor):
+// adds its bonded terms to its reciprocal-space force, after the gather has
+// stored that.  A kernel of its own, ahead of the integrator: the partners'
+// positions must be those of the step's start, and the integrator overwrites
+// them (summed there, an atom whose partner's wave had already stored saw the
+// new position).
+__global__ __launch_bounds__(256) void k_bonded_step(const LegDev* legs, BlockMap map) {
+  const int leg = find_leg(map, blockIdx.x);
+  const LegDev& g = legs[leg];
+  const long long i = (long long)(blockIdx.x - map.start[leg]) * blockDim.x + threadIdx.x;
+  if (i >= (long long)g.W * g.nba) return;
+  const int w = (int)(i / g.nba);
+  const int a = g.batoms[i - (long long)w * g.nba];
+  const v3 fb = bonded_force(g, w, a);
+  const size_t o = (size_t)w * g.n + a;
+  if (g.plain) {
+    // the plain form: the pair kernel adds to the same sums meanwhile
+    const size_t wn = (size_t)g.W * g.n;
+    unsafeAtomicAdd(&g.fd[o], (double)fb.x);
+    unsafeAtomicAdd(&g.fd[wn + o], (double)fb.y);
+    unsafeAtomicAdd(&g.fd[2 * wn + o], (double)fb.z);
+    return;
+  }
+  const int where = (w << 20) | a;
+  g.frx[o] += to_fixed((double)fb.x, kForceScale, g.err, kSiteBonded, where, g.leg_index);
+  g.fry[o] += to_fixed((double)fb.y, kForceScale, g.err, kSiteBonded, where, g.leg_index);
+  g.frz[o] += to_fixed((double)fb.z, kForceScale, g.err, kSiteBonded, where, g.leg_index);
+}
+
 // kick for one atom: returns v + dt F/m.  The total force (real-space terms
-// in fx/fy/fz, this step's reciprocal-space term and the bonded terms) is
-// stored back, so that fx/fy/fz hold the whole force of the step after the
+// in fx/fy/fz, this step's reciprocal-space and bonded terms in frx/fry/frz)
+// is stored back, so that fx/fy/fz hold the whole force of the step after the
 // call.
 __device__ __forceinline__ v3 kick(const LegDev& g, const StepArgs& S, int w, int a) {
   const size_t o = (size_t)w * g.n + a;
   const float acc = (float)kAccel / g.mass[a];
-  const v3 fb = bonded_force(g, w, a);
   if (g.plain) {
-    // the plain form: the step's pair and reciprocal forces were summed by
-    // FP64 atomics; read them, clear the sums for the next step
+    // the plain form: the step's forces were summed by FP64 atomics; read them,
+    // clear the sums for the next step
     const size_t wn = (size_t)g.W * g.n;
-    const double sx = g.fd[o] + (double)fb.x, sy = g.fd[wn + o] + (double)fb.y, sz = g.fd[2 * wn + o] + (double)fb.z;
+    const double sx = g.fd[o], sy = g.fd[wn + o], sz = g.fd[2 * wn + o];
     g.fd[o] = 0.0; g.fd[wn + o] = 0.0; g.fd[2 * wn + o] = 0.0;
     const int where = (w << 20) | a;
     g.fx[o] = to_fixed(sx, kForceScale, g.err, kSiteBonded, where, g.leg_index);
@@ -138,13 +166,7 @@ __device__ __forceinline__ v3 kick(const LegDev& g, const StepArgs& S, int w, in
     const float dt = S.dt;
     return mk(g.vx[o] + dt * (float)sx * acc, g.vy[o] + dt * (float)sy * acc, g.vz[o] + dt * (float)sz * acc);
   }
-  long long tx = g.fx[o] + g.frx[o], ty = g.fy[o] + g.fry[o], tz = g.fz[o] + g.frz[o];
-  if (fb.x != 0.f || fb.y != 0.f || fb.z != 0.f) {
-    const int where = (w << 20) | a;
-    tx += to_fixed((double)fb.x, kForceScale, g.err, kSiteBonded, where, g.leg_index);
-    ty += to_fixed((double)fb.y, kForceScale, g.err, kSiteBonded, where, g.leg_index);
-    tz += to_fixed((double)fb.z, kForceScale, g.err, kSiteBonded, where, g.leg_index);
-  }
+  const long long tx = g.fx[o] + g.frx[o], ty = g.fy[o] + g.fry[o], tz = g.fz[o] + g.frz[o];
   g.fx[o] = tx; g.fy[o] = ty; g.fz[o] = tz;
   const float F[3] = {(float)((double)tx * (1.0 / kForceScale)), (float)((double)ty * (1.0 / kForceScale)),
                       (float)((double)tz * (1.0 / kForceScale))};
@@ -250,6 +272,12 @@ __global__ __launch_bounds__(256) void k_integrate(const LegDev* legs, BlockMap 
 }
 
 }  // namespace
+
+void launch_bonded_step(hipStream_t s, const LegDev* d, const LegHost* h, int nl) {
+  BlockMap m;
+  const int nb = make_map(m, nl, [&](int i) { return (int)(((long long)h[i].W * h[i].nba + 255) / 256); });
+  if (nb) hipLaunchKernelGGL(k_bonded_step, dim3(nb), dim3(256), 0, s, d, m);
+}
 
 void launch_integrate(hipStream_t s, const LegDev* d, const LegHost* h, int nl, const long long* step,
                       const unsigned long long* seed, float dt, float temperature, float gamma) {
