@@ -20,7 +20,7 @@ namespace {
 
 struct Layout {
   size_t lam, lamS, rstate, free_atoms, lig_idx, aw_idx, fd, xr, yr, zr, flag, nbuild, maxdisp, wmax, hcell, box, ubox, rbforce, skin_used, bptr, bnb, bid, tptr, tid, batoms, mol_ptr, mol_atoms, baro, boxb, xb, yb, zb, molr, perm, cellcode, cellstart, cursor, xyzq, prm, bblo,
-      bbhi, gsten, lcount, lent, frx, fry, frz, grid64, cgrid, uflag, usph, uphi, tw[3], bmod[3], eacc, uacc, upart, lpart, ucst, total;
+      bbhi, gsten, lcount, lent, frx, fry, frz, grid64, cgrid, uflag, usph, phi, tw[3], bmod[3], eacc, uacc, upart, lpart, ucst, total;
 };
 
 struct Plan {
@@ -219,7 +219,7 @@ int make_plan(felis_ctx* c, const felis_leg* L, Plan& P) {
   y.grid64 = put(2 * (size_t)h.npair * h.Ktot * 8);
   y.cgrid = put((size_t)h.npair * h.Ktot * 8);
   y.usph = put(2 * (size_t)h.npair * 16);
-  y.uphi = put(2 * (size_t)h.npair * UknLines(h.K).size * 4);
+  y.phi = put(2 * (size_t)h.npair * PhiLines(h.K).size * 4);
   y.uflag = put((size_t)h.npair * h.K[2] * (ukn_chunks(h.K[1]) + 1) * 4);
   for (int d = 0; d < 3; ++d) { y.tw[d] = put(h.K[d] * 8); y.bmod[d] = put(h.K[d] * 4); }
   y.eacc = put(W * FELIS_NE * 8);
@@ -330,7 +330,7 @@ LegDev make_dev(const felis_ctx* c, const felis_leg* L, const Plan& p, const Met
   g.grid64 = (long long*)(w + y.grid64);
   g.cgrid = (float2*)(w + y.cgrid);
   g.usph = (float4*)(w + y.usph);
-  g.uphi = (float*)(w + y.uphi);
+  g.phi = (float*)(w + y.phi);
   g.uflag = (int*)(w + y.uflag);
   for (int d = 0; d < 3; ++d) { g.tw[d] = (float2*)(w + y.tw[d]); g.bmod[d] = (float*)(w + y.bmod[d]); }
   g.eacc = (long long*)(w + y.eacc);

@@ -160,7 +160,8 @@ struct LegDev {
                                         // atoms 4-7 (slot << 8 | 4-bit mask over the half's atoms)
   long long *frx, *fry, *frz;           // [W][n] reciprocal-space and bonded forces of the current MD step
   long long* grid64;                    // [2 npair][Ktot] u_kn ligand charge grids, fixed point
-  float* uphi;                          // [2 npair][UknLines size] u_kn: each frame's ligand potential
+  float* phi;                           // [2 npair][PhiLines size] potential of each window (u_kn: of each frame's
+                                        // ligand); slot w, or 2 w when every window has a complex grid of its own
   float4* usph;                         // [2 npair] u_kn: the ligand's bounding sphere per frame (centre, radius)
   int* uflag;                           // [npair][K2 (chunks + 1)] u_kn: 16-row chunks of each z plane, then the
                                         // planes themselves, that the frame's charges touch
@@ -182,13 +183,14 @@ __device__ __forceinline__ int* ukn_flags(const LegDev& g, int p) {
   return g.uflag + (size_t)p * g.K[2] * (ukn_chunks(g.K[1]) + 1);
 }
 
-// A u_kn frame's potential for the gather, in 128-byte lines of 4 x 4 x 2
-// points (x, y, z): an atom's 4 x 4 x 4 points lie in (1.75)^2 2.5 = 7.7 lines
-// on average, against some 19 of a row-major complex grid.
-struct UknLines {
+// A window's (u_kn: a frame's) potential as the gather reads it, in 128-byte
+// lines of 4 x 4 x 2 points (x, y, z): an atom's 4 x 4 x 4 points lie in
+// (1.75)^2 2.5 = 7.7 lines on average, against some 19 of a row-major complex
+// grid.
+struct PhiLines {
   int nx, ny, nz;                       // lines per axis
   int size;                             // floats
-  __host__ __device__ explicit UknLines(const int* K)
+  __host__ __device__ explicit PhiLines(const int* K)
       : nx((K[0] + 3) / 4), ny((K[1] + 3) / 4), nz((K[2] + 1) / 2), size(nx * ny * nz * 32) {}
   // a point's offset is the sum of its axes' parts
   __device__ __forceinline__ int x(int v) const { return (v >> 2) * 32 + (v & 3); }
@@ -261,6 +263,29 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ gptr<f32x4> as_global4(const float4* p) { return (gptr<f32x4>)p; }
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ gptr<f32x2> as_global2(const float2* p) { return (gptr<f32x2>)p; }
+
+// the value of the lane whose index differs by 1 (2) within the quad
+__device__ __forceinline__ float quad_xor1(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float quad_xor2(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));
+}
+// 4 x 4 transpose within the quad: lane k's r[m] becomes lane m's r[k]
+__device__ __forceinline__ void quad_transpose(float (&r)[4], bool b0, bool b1) {
+#pragma unroll
+  for (int h = 0; h < 4; h += 2) {
+    const float u = quad_xor1(b0 ? r[h] : r[h + 1]);
+    r[h] = b0 ? u : r[h];
+    r[h + 1] = b0 ? r[h + 1] : u;
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const float u = quad_xor2(b1 ? r[h] : r[h + 2]);
+    r[h] = b1 ? u : r[h];
+    r[h + 2] = b1 ? r[h + 2] : u;
+  }
+}
 
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {

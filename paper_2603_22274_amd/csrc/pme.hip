@@ -19,8 +19,6 @@
 // multiplication by G and inverse transform.
 #include <algorithm>
 
-#include <climits>
-
 #include "felis_internal.h"
 
 namespace felis {
@@ -239,8 +237,9 @@ __device__ __forceinline__ float2* fft_lines(float2* src, float2* dst, int n, co
 //       a few dozen ligand atoms, 4 forward (y axis) and 5 as 3: only the rows
 //       that the charges touch (uflag) are read and transformed, what was not
 //       touched counts as zero.  2 skips untouched chunks likewise.  6 as 1 on
-//       the x axis, but the two frames' potentials go to uphi, each by itself
-//       in lines of 4 x 4 x 2 points for the gather.
+//       the x axis, the last pass: the potentials of the grid's two windows
+//       (frames) go to phi, each by itself in lines of 4 x 4 x 2 points for the
+//       gather.
 template <int AXIS, int FORM, int LINES>
 __global__ __launch_bounds__(256) void k_fft(const LegDev* legs, BlockMap map, int ukn) {
   constexpr int MODE = FORM == 4 ? 0 : (FORM == 5 ? 3 : (FORM == 6 ? 1 : FORM));
@@ -393,9 +392,10 @@ __global__ __launch_bounds__(256) void k_fft(const LegDev* legs, BlockMap map, i
   }
   if (FORM == 6) {
     // 4 x 4 points (x, y) of the plane are half a line: 16 consecutive threads
-    const UknLines l(g.K);
-    float* re = g.uphi + (size_t)(2 * p) * l.size;
+    const PhiLines l(g.K);
+    float* re = g.phi + (size_t)(2 * p) * l.size;
     float* im = re + l.size;
+    const bool two = ukn ? ukn == 1 : g.pack != 0;       // two windows (frames) to a grid
     const int nq = l.nx * (LINES / 4);
     for (int idx = threadIdx.x; idx < nq * 16; idx += blockDim.x) {
       const int q = idx >> 4, qy = q / l.nx, e = 4 * (q - qy * l.nx) + (idx & 3), b = 4 * qy + ((idx >> 2) & 3);
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(256) void k_fft(const LegDev* legs, BlockMap map, i
       const float2 v = conj2(res[e * LINES + b]);
       const int at = l.x(e) + l.y(y) + l.z(o);
       re[at] = v.x;
-      if (ukn == 1) im[at] = v.y;
+      if (two) im[at] = v.y;
     }
     return;
   }
@@ -511,11 +511,27 @@ __global__ __launch_bounds__(kXYThreads) void k_fft_xy(const LegDev* legs, Block
   }
   __syncthreads();
   r = fft_lines_nl(o, r, Ky, dly, g.rad[1], g.nrad[1], twy);
+  if (INVERSE) {
+    // the potentials in the gather's lines: 4 x 4 points of the plane (half a
+    // line) to 16 consecutive threads
+    const PhiLines l(g.K);
+    float* re = g.phi + (size_t)(2 * p) * l.size;
+    float* im = re + l.size;
+    const FastDiv dnx(l.nx);
+    for (int idx = threadIdx.x; idx < l.nx * l.ny * 16; idx += blockDim.x) {
+      const int q = idx >> 4, qy = dnx.div(q);
+      const int x = 4 * (q - qy * l.nx) + (idx & 3), y = 4 * qy + ((idx >> 2) & 3);
+      if (x >= Kx || y >= Ky) continue;
+      const float2 v = conj2(r[y * nly + x]);
+      const int at = l.x(x) + l.y(y) + l.z(z);
+      re[at] = v.x;
+      if (g.pack) im[at] = v.y;
+    }
+    return;
+  }
   for (int idx = threadIdx.x; idx < np; idx += blockDim.x) {
     const int y = dKx.div(idx), x = idx - y * Kx;
-    float2 v = r[y * nly + x];                                      // [y][x] = grid order
-    if (INVERSE) v = conj2(v);
-    cg[idx] = v;
+    cg[idx] = r[y * nly + x];                                       // [y][x] = grid order
   }
 }
 
@@ -752,11 +768,16 @@ __global__ __launch_bounds__(256) void k_spread(const LegDev* legs, BlockMap map
   }
 }
 
-// Each gather block stages its 64 atoms' stencil region of the grid in LDS
-// (rows read contiguously) instead of 64 scattered reads per atom; the forces
-// are bitwise the same (42-window complex leg: 5.40 -> 5.34 ms per MD step)
-constexpr int kGatherTile = 4096;              // grid points staged per block (16 KB)
-
+// Forces of the reciprocal part, four lanes per atom, atoms in the
+// neighbour-list sort order (spatially coherent).  A quad reads 4 neighbours
+// (lane k the point at x - k) of one row of the window's potential at a time,
+// a transpose within the quad hands lane k the rows of plane z - k, and lane k
+// sums its 16 points.  The potential lies in 128-byte lines of 4 x 4 x 2
+// points, 7.7 to an atom's stencil, which neighbouring atoms share in L1.
+// 42 windows of 70,527 atoms on 96^3: 232 us alone; 365 us when each block of
+// 64 atoms staged the box around their stencils in LDS from the complex grid
+// (16 points a thread, each with its index arithmetic).  Beside the pair
+// kernel inside a step: 1,290 -> 300 us.
 // STEP: store the force in frx/fry/frz (the integrator adds it to the
 // real-space force) instead of adding it to fx/fy/fz
 template <bool ENERGY, bool STEP>
@@ -766,8 +787,6 @@ __global__ __launch_bounds__(256) void k_gather(const LegDev* legs, BlockMap map
   // grid sizes in scalar registers (otherwise reloaded from memory inside the loops)
   const int K[3] = {__builtin_amdgcn_readfirstlane(g.K[0]), __builtin_amdgcn_readfirstlane(g.K[1]),
                     __builtin_amdgcn_readfirstlane(g.K[2])};
-  // atoms in the neighbour-list sort order (spatially coherent); 4 lanes per
-  // atom, lane iz sums the 16 stencil points of plane z = bz - iz
   // blocks never straddle two windows: the block's 64 atoms share one grid
   const int bpw = (g.npad + 63) >> 6;
   const int blk = blockIdx.x - map.start[leg];
@@ -780,121 +799,53 @@ __global__ __launch_bounds__(256) void k_gather(const LegDev* legs, BlockMap map
   const bool valid = slot < g.npad && ap >= 0;
   const int a = ap >= 0 ? ap : 0;
   const int iz = threadIdx.x & 3;
+  const bool b0 = iz & 1, b1 = iz & 2;
   const size_t o = (size_t)w * g.n + a;
-  const float q = g.xyzq[lc].w * kInvSqrtKE;    // the window's charge (packed times sqrt(KE))
   const float4 st = g.gsten[lc];               // stencil offsets and bases (from the pack)
+  const PhiLines ln(K);
+  const gptr<float> phi = as_global(g.phi + (size_t)(g.pack ? w : 2 * w) * ln.size);
   int bb[3];
   unpack_bases(st.w, bb);
-  int bx = bb[0], by = bb[1], bz = bb[2];
+  int gx = bb[0] - iz; if (gx < 0) gx += K[0];
+  int plane[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) { plane[m] = bb[2] - m; if (plane[m] < 0) plane[m] += K[2]; plane[m] = ln.z(plane[m]); }
+  float r[4][4];
+#pragma unroll
+  for (int iy = 0; iy < 4; ++iy) {
+    int gy = bb[1] - iy; if (gy < 0) gy += K[1];
+    const int xy = ln.x(gx) + ln.y(gy);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) r[iy][m] = phi[xy + plane[m]];
+  }
+  const float q = g.xyzq[lc].w * kInvSqrtKE;    // the window's charge (packed times sqrt(KE))
   float wx[4], wy[4], wz[4], dx[4], dy[4], dz[4];
   bspline4(st.x, wx, dx);
   bspline4(st.y, wy, dy);
   bspline4(st.z, wz, dz);
-  const bool im = g.pack && (w & 1);
   float p0 = 0.f, px = 0.f, py = 0.f;          // sum w phi, sum dwx phi, sum dwy phi over the plane
-  // Stage the block's stencil region of the window's grid component in LDS
-  // (rows read contiguously), then interpolate from LDS.  Bases are unwrapped
-  // to the periodic image nearest the block's first atom's; a region larger
-  // than the tile (atoms spread over the box) reads the grid directly.
-  __shared__ float s_tile[kGatherTile];
-  __shared__ int s_red[4][6];
-  __shared__ int s_ref[3];
-  if (threadIdx.x == 0) {
-    int r[3];
-    unpack_bases(g.gsten[(size_t)w * g.npad + s0].w, r);
-    s_ref[0] = r[0]; s_ref[1] = r[1]; s_ref[2] = r[2];
-  }
-  __syncthreads();
-  {
-    const int ref[3] = {s_ref[0], s_ref[1], s_ref[2]};
-    int* bp[3] = {&bx, &by, &bz};
-    for (int d = 0; d < 3; ++d) {
-      const int df = *bp[d] - ref[d];
-      if (2 * df > K[d]) *bp[d] -= K[d];
-      else if (2 * df < -K[d]) *bp[d] += K[d];
-    }
-  }
-  int mn[3] = {valid ? bx : INT_MAX, valid ? by : INT_MAX, valid ? bz : INT_MAX};
-  int mx[3] = {valid ? bx : INT_MIN, valid ? by : INT_MIN, valid ? bz : INT_MIN};
-  for (int off = 1; off < 64; off <<= 1)
-    for (int d = 0; d < 3; ++d) {
-      mn[d] = min(mn[d], __shfl_xor(mn[d], off, 64));
-      mx[d] = max(mx[d], __shfl_xor(mx[d], off, 64));
-    }
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0)
-    for (int d = 0; d < 3; ++d) { s_red[wave][d] = mn[d]; s_red[wave][3 + d] = mx[d]; }
-  __syncthreads();
-  int lo[3], nd[3];
-  for (int d = 0; d < 3; ++d) {
-    int a0 = s_red[0][d], a1 = s_red[0][3 + d];
-    for (int k = 1; k < 4; ++k) { a0 = min(a0, s_red[k][d]); a1 = max(a1, s_red[k][3 + d]); }
-    lo[d] = a0 - 3;
-    nd[d] = a1 - lo[d] + 1;
-  }
-  const int vol = nd[0] * nd[1] * nd[2];     // block-uniform (the first atom is valid)
-  if (!valid) { bx = lo[0] + 3; by = lo[1] + 3; bz = lo[2] + 3; }   // in-tile reads, results unused
-  const float* comp = reinterpret_cast<const float*>(g.cgrid + (size_t)(g.pack ? w >> 1 : w) * g.Ktot) + (im ? 1 : 0);
-  if (vol <= kGatherTile) {
-    for (int e = threadIdx.x; e < vol; e += 256) {
-      const int x = e % nd[0], yz = e / nd[0];
-      const int y = yz % nd[1], z = yz / nd[1];
-      int gx = lo[0] + x, gy = lo[1] + y, gz = lo[2] + z;
-      gx += gx < 0 ? K[0] : (gx >= K[0] ? -K[0] : 0);
-      gy += gy < 0 ? K[1] : (gy >= K[1] ? -K[1] : 0);
-      gz += gz < 0 ? K[2] : (gz >= K[2] ? -K[2] : 0);
-      s_tile[e] = comp[2 * (((size_t)gz * K[1] + gy) * K[0] + gx)];
-    }
-    __syncthreads();
-    const int zb = (bz - iz - lo[2]) * nd[1];
 #pragma unroll
-    for (int iy = 0; iy < 4; ++iy) {
-      const float* row = s_tile + (zb + by - iy - lo[1]) * nd[0] + (bx - lo[0]);
-      float s0v = 0.f, s1 = 0.f;
+  for (int iy = 0; iy < 4; ++iy) {
+    quad_transpose(r[iy], b0, b1);
+    float s0v = 0.f, s1 = 0.f;
 #pragma unroll
-      for (int ix = 0; ix < 4; ++ix) {
-        const float phi = row[-ix];
-        s0v = fmaf(wx[ix], phi, s0v);
-        s1 = fmaf(dx[ix], phi, s1);
-      }
-      p0 = fmaf(wy[iy], s0v, p0);
-      px = fmaf(wy[iy], s1, px);
-      py = fmaf(dy[iy], s0v, py);
+    for (int ix = 0; ix < 4; ++ix) {
+      s0v = fmaf(wx[ix], r[iy][ix], s0v);
+      s1 = fmaf(dx[ix], r[iy][ix], s1);
     }
-  } else {
-    // wrap the unwrapped bases back into the grid and read it directly
-    bx += bx < 0 ? K[0] : (bx >= K[0] ? -K[0] : 0);
-    by += by < 0 ? K[1] : (by >= K[1] ? -K[1] : 0);
-    bz += bz < 0 ? K[2] : (bz >= K[2] ? -K[2] : 0);
-    int gz = bz - iz; if (gz < 0) gz += K[2];
-    int gxv[4];
-#pragma unroll
-    for (int ix = 0; ix < 4; ++ix) { gxv[ix] = bx - ix; if (gxv[ix] < 0) gxv[ix] += K[0]; }
-    const float2* plane = g.cgrid + (size_t)(g.pack ? w >> 1 : w) * g.Ktot + (size_t)gz * K[1] * K[0];
-#pragma unroll
-    for (int iy = 0; iy < 4; ++iy) {
-      int gy = by - iy; if (gy < 0) gy += K[1];
-      const float2* row = plane + (size_t)gy * K[0];
-      float s0v = 0.f, s1 = 0.f;
-#pragma unroll
-      for (int ix = 0; ix < 4; ++ix) {
-        const float2 c = row[gxv[ix]];
-        const float phi = im ? c.y : c.x;
-        s0v = fmaf(wx[ix], phi, s0v);
-        s1 = fmaf(dx[ix], phi, s1);
-      }
-      p0 = fmaf(wy[iy], s0v, p0);
-      px = fmaf(wy[iy], s1, px);
-      py = fmaf(dy[iy], s0v, py);
-    }
+    p0 = fmaf(wy[iy], s0v, p0);
+    px = fmaf(wy[iy], s1, px);
+    py = fmaf(dy[iy], s0v, py);
   }
-  float pot = p0 * wz[iz], gxs = px * wz[iz], gys = py * wz[iz], gzs = p0 * dz[iz];
-  for (int off = 1; off < 4; off <<= 1) {
-    pot += __shfl_xor(pot, off, 64);
-    gxs += __shfl_xor(gxs, off, 64);
-    gys += __shfl_xor(gys, off, 64);
-    gzs += __shfl_xor(gzs, off, 64);
-  }
+  const float wzk = iz == 0 ? wz[0] : (iz == 1 ? wz[1] : (iz == 2 ? wz[2] : wz[3]));
+  const float dzk = iz == 0 ? dz[0] : (iz == 1 ? dz[1] : (iz == 2 ? dz[2] : dz[3]));
+  // sums over the four planes
+  auto planes = [](float v, float s) {
+    float t = fmaf(v, s, quad_xor1(v * s));
+    t += quad_xor2(t);
+    return t;
+  };
+  const float pot = planes(p0, wzk), gxs = planes(px, wzk), gys = planes(py, wzk), gzs = planes(p0, dzk);
   const int sub = iz;
   if (valid && sub == 0) {
     const BoxW& B = g.box[w];
@@ -923,18 +874,10 @@ __global__ __launch_bounds__(256) void k_gather(const LegDev* legs, BlockMap map
   }
   if (ENERGY) {
     double e = (valid && sub == 0) ? 0.5 * (double)q * (double)pot : 0.0;
-    const int lane = threadIdx.x & 63;
-    const int w0 = __shfl(w, 0, 64);
-    const bool same = __ballot(valid && w != w0) == 0ull;
-    if (same) {
-      e = wave_sum(e);
-      if (lane == 0)
-        atomicAdd((unsigned long long*)&g.eacc[(size_t)w0 * FELIS_NE + FELIS_E_RECIP],
-                  (unsigned long long)to_fixed(e, kEnergyScale, g.err));
-    } else if (valid && sub == 0) {
+    e = wave_sum(e);
+    if ((threadIdx.x & 63) == 0)
       atomicAdd((unsigned long long*)&g.eacc[(size_t)w * FELIS_NE + FELIS_E_RECIP],
                 (unsigned long long)to_fixed(e, kEnergyScale, g.err));
-    }
   }
 }
 
@@ -1035,7 +978,7 @@ void launch_pme_fft(hipStream_t s, const LegDev* d, const LegHost* h, int nl, in
   fft_pass<1, 0>(s, d, h, nl, 0);
   fft_pass<2, 3>(s, d, h, nl, 0);
   fft_pass<1, 1>(s, d, h, nl, 0);
-  fft_pass<0, 1>(s, d, h, nl, 0);
+  fft_pass<0, 6>(s, d, h, nl, 0);
 }
 
 void launch_pme(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool energy, bool step_forces) {

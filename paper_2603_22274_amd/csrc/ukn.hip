@@ -138,31 +138,8 @@ template <int AXIS>
 __device__ __forceinline__ int quad_from(int v) {
   return __builtin_amdgcn_update_dpp(0, v, AXIS * 0x55, 0xf, 0xf, true);
 }
-// the value of the lane whose index differs by 1 (2) within the quad
-__device__ __forceinline__ float quad_xor1(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float quad_xor2(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));
-}
-// 4 x 4 transpose within the quad: lane k's r[m] becomes lane m's r[k]
-__device__ __forceinline__ void quad_transpose(float (&r)[4], bool b0, bool b1) {
-#pragma unroll
-  for (int h = 0; h < 4; h += 2) {
-    const float u = quad_xor1(b0 ? r[h] : r[h + 1]);
-    r[h] = b0 ? u : r[h];
-    r[h + 1] = b0 ? r[h + 1] : u;
-  }
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const float u = quad_xor2(b1 ? r[h] : r[h + 2]);
-    r[h] = b1 ? u : r[h];
-    r[h + 2] = b1 ? r[h + 2] : u;
-  }
-}
-
 // items: frame x block of 256 atoms, 4 lanes per atom, 64 atoms per pass:
-// phi_b of frame f (uphi) at every atom;
+// phi_b of frame f (phi) at every atom;
 // E_LE += a phi_b, E_LL += b phi_b / 2 over all atoms.  The FP64 grid position
 // and the spline weights of an axis are the work here (an atom's 64 points are
 // 64 FMAs): lane k of the quad makes those of axis k and the quad shares them.
@@ -171,7 +148,7 @@ __device__ __forceinline__ void quad_transpose(float (&r)[4], bool b0, bool b1) 
 // quad hands lane k the rows of plane z - k, and it sums them.  42 frames of
 // 70,527 atoms: 389 us with 16 lanes an atom, each making all three axes; 290
 // us with lane k reading its own plane's rows of the complex grid, 181 us from
-// uphi's 128-byte lines.
+// phi's 128-byte lines.
 __global__ __launch_bounds__(256) void k_ukn_gather(const LegDev* legs, UknArgs A) {
 #pragma clang fp contract(off)
   const LegDev& g = legs[0];
@@ -179,8 +156,8 @@ __global__ __launch_bounds__(256) void k_ukn_gather(const LegDev* legs, UknArgs 
   const int f = blockIdx.x / nb;
   const int a0 = (blockIdx.x - f * nb) * 256 + (threadIdx.x >> 2);
   const int iz = threadIdx.x & 3;
-  const UknLines ln(g.K);
-  const float* phi = g.uphi + (size_t)(A.upk ? 2 * f : f) * ln.size;
+  const PhiLines ln(g.K);
+  const float* phi = g.phi + (size_t)(A.upk ? 2 * f : f) * ln.size;
   const BoxW& B = g.ubox[f];
   const size_t fo = (size_t)(A.f0 + f) * A.stride;
   const float* pos = iz == 0 ? A.fx : (iz == 1 ? A.fy : A.fz);
