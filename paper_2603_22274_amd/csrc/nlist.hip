@@ -14,15 +14,50 @@
 namespace felis {
 namespace {
 
-constexpr int kCellOf = 4096;                 // candidates per table window in k_build
-constexpr int kBuildWaves = 2;                // waves per list-build workgroup
-constexpr int kBuildThreads = 64 * kBuildWaves;
+constexpr int kBloomWords = 1024;             // 32-bit words of k_build's filter of own and excluded atoms
+constexpr int kTabOf = 4096;                  // candidates per table window in k_build
+// Most cluster pairs in a launch for four waves a pair: every wave repeats the
+// pair's set-up and the round's (a sixth of a pair's work), so one wave does
+// the least work and four end soonest where the pairs alone do not fill the
+// chip.  One | four waves: 504 pairs 15.8 | 10.0 us, 9,440 (20 windows of 7,540
+// atoms) 108 | 82, 39,000 245 | 290, 185,000 (42 windows of 70,527) 786 | 1418
+constexpr int kFewPairs = 16384;
+constexpr float kFar = 1.0e30f;               // squared distance that no test passes
 
 // a wave-uniform float moved to a scalar register
 __device__ __forceinline__ float scalar(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
+// Rows of 16 lanes.  out[k] holds v's row k in every row.
+__device__ __forceinline__ void spread_rows(unsigned v, unsigned out[4]) {
+  const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);       // rows 0 1 0 1 | 2 3 2 3
+  const auto a = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+  out[0] = a[0];
+  out[1] = a[1];
+  out[2] = b[0];
+  out[3] = b[1];
+}
+// v[k]'s row r to v[r]'s row k
+__device__ __forceinline__ void transpose_rows(float v[4]) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[0]), __float_as_uint(v[2]), false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[1]), __float_as_uint(v[3]), false, false);
+  const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+  const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+  v[0] = __uint_as_float(c[0]);
+  v[1] = __uint_as_float(c[1]);
+  v[2] = __uint_as_float(d[0]);
+  v[3] = __uint_as_float(d[1]);
+}
+// the value N lanes before in the row (0 at its start); the row's last value
+template <int N>
+__device__ __forceinline__ unsigned row_shr(unsigned v) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x110 + N, 0xF, 0xF, true);
+}
+__device__ __forceinline__ unsigned row_last(unsigned v) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x15F, 0xF, 0xF, true);
+}
 __device__ __forceinline__ int cell_of(float v, float L, float invL, int n) {
   float u = wrapf(v, L, invL) * invL;
   int c = (int)(u * (float)n);
@@ -335,131 +370,147 @@ __global__ __launch_bounds__(1024) void k_check_sort(const LegDev* legs, BlockMa
 
 bool sort_in_lds(const LegHost& h) { return h.ncell <= kSortCells && h.n <= kSortAtoms; }
 
-// One workgroup per cluster: sweep the coarse blocks (aligned 2x2x2 fine
-// cells) within r_list of the cluster's box, kBuildThreads blocks per round,
-// each trimmed to the Hilbert span of its fine cells within r_list, and list
-// every atom j with at least one i of the cluster in range.  The waves take
-// consecutive 64-candidate parts of each step and append in wave order, so
-// the list order is fixed (cells in sweep order, slots ascending).  Two waves
-// per workgroup: every wave repeats the cluster's set-up (~700 instructions),
-// so four waves spent 15 % more and one wave pays the per-round scan and
-// table work twice as often.
-__global__ __launch_bounds__(kBuildThreads) void k_build(const LegDev* legs, BlockMap map) {
+// One workgroup per pair of consecutive clusters (16 atoms): sweep the coarse
+// blocks (aligned 2x2x2 fine cells) within r_list of the pair's box, one block
+// a lane and round, each trimmed to the Hilbert span of its fine cells within
+// r_list, and list every atom j with at least one i of a half-cluster in
+// range.  The waves take consecutive 64-candidate parts of each step and
+// append in wave order, so the list order is fixed (cells in sweep order,
+// slots ascending).
+//
+// The distance test is a contraction: with r relative to the pair's first
+// atom, |r_j - r_i|^2 - (r_list + 0.01)^2 = (-2 r_i, 1) . (r_j, |r_j|^2 - inc2)
+// + |r_i|^2, so one 16x16x4 FP32 matrix product tests 16 candidates against
+// the 16 atoms, and it leaves a lane with exactly one half-cluster's four
+// results (row 4 g + r: atom r of half-cluster g).  Four of them serve a
+// wave's 64 candidates, which are brought from one lane a candidate to one row
+// a component by four lane-row swaps.  Vector issue bounds it (0.83 wave
+// instructions per SIMD and 4 cycles): about 115 instructions for 64
+// candidates and 16 atoms, most of them to form masks and places of entries,
+// 1,000 for a pair's set-up and rounds.  A list of every window of 42 x 70,527
+// atoms takes 2.3 ms; it took 4.2 ms with one workgroup of two waves a
+// cluster, eight tests of three FMAs a candidate, a byte table of the
+// candidates' blocks and a search of the exclusions by each lane.
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 1 ? 6 : 5) void k_build(const LegDev* legs, BlockMap map) {
+  static_assert(WAVES <= 4, "a step's counts lie in one word a list");
+  constexpr int kThreads = 64 * WAVES;
   const int leg = find_leg(map, blockIdx.x);
   const LegDev& g = legs[leg];
-  const long long item = (long long)blockIdx.x - map.start[leg];
-  const int w = (int)(item / g.nclus);
+  const int npair = (g.nclus + 1) >> 1;
+  const unsigned b = blockIdx.x - (unsigned)map.start[leg];
+  const int w = (int)(b / (unsigned)npair);
   if (!g.flag[w]) return;                       // uniform over the block
-  const int c = (int)(item - (long long)w * g.nclus);
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int c = 2 * (int)(b - (unsigned)w * (unsigned)npair);    // the pair's first cluster
+  const size_t item = (size_t)w * g.nclus + c;
+  const int tid = threadIdx.x, wave = WAVES > 1 ? tid >> 6 : 0, lane = tid & 63;
+  const int row = lane >> 4, col = lane & 15;   // matrix layout: half-cluster (or component), candidate
 
-  __shared__ int s_ai[kClus];
-  __shared__ float s_xi[kClus][3];
-  __shared__ int s_ex[kClus][kMaxExcl];
-  __shared__ int s_nex[kClus];
-  __shared__ unsigned s_bloom[64];              // 2048-bit filter of excluded atoms
-  __shared__ int s_start[kBuildThreads];        // first sorted slot of each block in the round
-  __shared__ int s_pre[kBuildThreads];          // exclusive prefix of candidate counts
-  __shared__ int s_wsum[kBuildWaves];
-  __shared__ int s_wc[2][2][kBuildWaves];
-  __shared__ unsigned char s_cellof[kCellOf];   // candidate -> block of the round, one window at a time
-  const size_t o = (size_t)w * g.n;
-  const int* perm = g.perm + (size_t)w * g.npad;
-  if (tid < 64) s_bloom[tid] = 0u;
-  __syncthreads();
-  if (tid < kClus) {
-    const int a = perm[c * kClus + tid];
-    s_ai[tid] = a;
-    int ne = 0;
-    // a padding slot gets defined (zero) coordinates: nothing downstream may
-    // depend on what an earlier workgroup left in LDS
-    s_xi[tid][0] = 0.f;
-    s_xi[tid][1] = 0.f;
-    s_xi[tid][2] = 0.f;
-    if (a >= 0) {
-      s_xi[tid][0] = g.x[o + a];
-      s_xi[tid][1] = g.y[o + a];
-      s_xi[tid][2] = g.z[o + a];
-      const int e0 = g.excl_ptr[a], e1 = g.excl_ptr[a + 1];
-      ne = e1 - e0;
-      if (ne > kMaxExcl) { latch(g.err, kErrExcl, kSiteExclCount, (w << 20) | a, g.leg_index); ne = kMaxExcl; }
-      for (int k = 0; k < ne; ++k) {
-        const int e = g.excl_idx[e0 + k];
-        s_ex[tid][k] = e;
-        atomicOr(&s_bloom[(e >> 5) & 63], 1u << (e & 31));
-      }
-    }
-    s_nex[tid] = ne;
-  }
-  __syncthreads();
+  __shared__ unsigned s_bloom[kBloomWords];     // filter of the pair's own and excluded atoms
+  __shared__ unsigned long long s_bits[kTabOf / 64];  // candidates whose successor opens a new block
+  __shared__ int s_delta[kThreads];             // per non-empty block of the round: slot - candidate
+  __shared__ int s_wsum[WAVES], s_wblk[WAVES];
+  __shared__ unsigned s_wc[2][4];               // entries of a step: byte per list and wave
+  __shared__ float4 s_xi[16];
+  __shared__ float s_ni[16];
+
+  const size_t o = (size_t)w * g.npad;
+  const gptr<int> perm = as_global(g.perm + o);
+  const gptr<f32x4> xq = as_global4(g.xyzq + o);
+  const int n = g.n, cap = g.cap, slot0 = c * kClus, nf = g.ncoarse, nbits = g.nbits;
+  const gptr<int> cst = as_global(g.cellstart + (size_t)w * (g.ncell + 1));
+  const gptr<unsigned> hcell = as_global(g.hcell);
+  const bool two = c + 1 < g.nclus;
+  const float4 lo0 = g.bblo[item], hi0 = g.bbhi[item], lo1 = g.bblo[item + two], hi1 = g.bbhi[item + two];
+  // the four lists (halves of the first, then of the second cluster) lie one
+  // after the other; each lane appends to its row's
+  typedef __attribute__((address_space(1))) char gchar;
+  gchar* const lists = (gchar*)(g.lent + item * 2 * cap);
 
   // box edges in scalar registers: read once, not again after every list store
   const BoxW& B = g.box[w];
   const float Lf[3] = {scalar(B.Lf[0]), scalar(B.Lf[1]), scalar(B.Lf[2])};
   const float iLf[3] = {scalar(B.invLf[0]), scalar(B.invLf[1]), scalar(B.invLf[2])};
-  const int cap = __builtin_amdgcn_readfirstlane(g.cap);
-  const float4 lo4 = g.bblo[item], hi4 = g.bbhi[item];
-  const float lo[3] = {lo4.x, lo4.y, lo4.z}, hi[3] = {hi4.x, hi4.y, hi4.z};
-  const int nf = g.ncoarse;
-  const float pre = (float)g.rlist + 0.05f;
+  const float rlist = scalar((float)g.rlist), incl = rlist + 0.01f;
+  const float inc2 = incl * incl;
+
+  // the pair's atoms: atom col of the pair in every row
+  const int si = slot0 + col;
+  const f32x4 xi = xq[min(si, n - 1)];
+  // exclusions: column i holds those of atom i, the first four in its four
+  // rows and the others in the second register
+  int ex[2] = {-1, -1}, own = -1;
+  if (si < n) {
+    own = perm[si];
+    const int e0 = g.excl_ptr[own], ne = g.excl_ptr[own + 1] - e0;
+    for (int h = 0; h < 2; ++h)
+      if (4 * h + row < ne) ex[h] = g.excl_idx[e0 + 4 * h + row];
+    if (ne > kMaxExcl && tid < 16) latch(g.err, kErrExcl, kSiteExclCount, (w << 20) | own, g.leg_index);
+  }
+  for (int k = tid; k < kBloomWords; k += kThreads) s_bloom[k] = 0u;
+  if (tid < 8) s_wc[tid >> 2][tid & 3] = 0u;
+  __syncthreads();
+  if (wave == 0) {
+    auto put = [&](int a) { atomicOr(&s_bloom[(a >> 5) & (kBloomWords - 1)], 1u << (a & 31)); };
+    for (int h = 0; h < 2; ++h)
+      if (ex[h] >= 0) put(ex[h]);
+    if (row == 0 && si < n) put(own);
+  }
+
+  // positions relative to the first atom (always a real one), nearest image
+  float ri[3], x0[3];
+  bool near = true;
+  for (int d = 0; d < 3; ++d) {
+    x0[d] = scalar(xi[d]);
+    const float v = xi[d] - x0[d];
+    ri[d] = __fmaf_rn(-Lf[d], rintf(v * iLf[d]), v);
+    // one periodic image per candidate (taken against the first atom) is the
+    // nearest image for every i whenever extent + r_list + margin < L/2
+    near = near && fabsf(ri[d]) + incl + 0.02f < 0.5f * Lf[d];
+  }
+  float ni = __fmaf_rn(ri[0], ri[0], __fmaf_rn(ri[1], ri[1], ri[2] * ri[2]));
+  const bool real = si < n && ni < kFar;        // false for a padding slot and for a NaN position
+  const bool shift = __ballot(si < n && !near) == 0ull;
+  ni = real ? ni : kFar;
+  // (in the frame of the first atom |r| < r_list + the pair's extent where it
+  // counts, so the FP32 error of the expanded form stays below 1e-3 A^2, far
+  // inside the margin of 0.01 A, 0.2 A^2)
+  const float am = !real ? 0.f : row == 0 ? -2.0f * ri[0] : row == 1 ? -2.0f * ri[1] : row == 2 ? -2.0f * ri[2] : 1.0f;
+  if (tid < 16) {
+    s_xi[tid] = make_float4(xi[0], xi[1], xi[2], real ? 0.f : kFar);
+    s_ni[tid] = ni;
+  }
+  __syncthreads();
+  const f32x4 ci = {s_ni[4 * row], s_ni[4 * row + 1], s_ni[4 * row + 2], s_ni[4 * row + 3]};
+
+  const float lo[3] = {scalar(fminf(lo0.x, lo1.x)), scalar(fminf(lo0.y, lo1.y)), scalar(fminf(lo0.z, lo1.z))};
+  const float hi[3] = {scalar(fmaxf(hi0.x, hi1.x)), scalar(fmaxf(hi0.y, hi1.y)), scalar(fmaxf(hi0.z, hi1.z))};
+  const float pre = rlist + 0.05f;
   const float pre2 = pre * pre;
   int r0[3], nC[3];
   bool full[3];
-  float cen[3], half[3], csd[3];
+  float csd[3];
   for (int d = 0; d < 3; ++d) {
-    cen[d] = 0.5f * (lo[d] + hi[d]);
-    half[d] = 0.5f * (hi[d] - lo[d]);
-    if (!(half[d] >= 0.f && half[d] <= Lf[d])) { cen[d] = 0.f; half[d] = Lf[d]; }   // no valid atom
+    float cen = 0.5f * (lo[d] + hi[d]), half = 0.5f * (hi[d] - lo[d]);
+    if (!(half >= 0.f && half <= Lf[d])) { cen = 0.f; half = Lf[d]; }   // no valid atom
     // nf is a power of two: exact cell edge; the range ends use its inverse
     // (a rounding flip only adds or drops a cell whose nearest face lies
     // pre - r_list - 0.01 = 0.04 A beyond the list radius)
-    const float cs = ldexpf(Lf[d], 1 - g.nbits);
-    const float ics = ldexpf(iLf[d], g.nbits - 1);
-    csd[d] = cs;
-    const int a0 = (int)floorf((cen[d] - half[d] - pre) * ics);
-    const int a1 = (int)floorf((cen[d] + half[d] + pre) * ics);
-    full[d] = a1 - a0 + 1 >= nf;               // the range wraps onto itself: every cell, no gap test
-    r0[d] = full[d] ? 0 : a0;
-    nC[d] = full[d] ? nf : a1 - a0 + 1;
+    const float cs = ldexpf(Lf[d], 1 - nbits);
+    const float ics = ldexpf(iLf[d], nbits - 1);
+    csd[d] = scalar(cs);
+    const int a0 = (int)floorf((cen - half - pre) * ics);
+    const int a1 = (int)floorf((cen + half + pre) * ics);
+    full[d] = __builtin_amdgcn_readfirstlane(a1 - a0 + 1 >= nf);   // the range wraps onto itself: every cell, no gap test
+    r0[d] = __builtin_amdgcn_readfirstlane(full[d] ? 0 : a0);
+    nC[d] = __builtin_amdgcn_readfirstlane(full[d] ? nf : a1 - a0 + 1);
   }
-  const float4* __restrict__ xq = g.xyzq + (size_t)w * g.npad;
-  const float incl = (float)g.rlist + 0.01f;
-  const float inc2 = incl * incl;
-  float xi[kClus][3], ri[kClus][3];
-  int ai[kClus];
-  float ext[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-  for (int ii = 0; ii < kClus; ++ii) {
-    ai[ii] = __builtin_amdgcn_readfirstlane(s_ai[ii]);           // uniform: scalar registers
-    for (int d = 0; d < 3; ++d) {
-      xi[ii][d] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_xi[ii][d])));
-      // position relative to the cluster's first atom (always a real atom), nearest image
-      const float v = xi[ii][d] - xi[0][d];
-      ri[ii][d] = __fmaf_rn(-Lf[d], rintf(v * iLf[d]), v);
-      if (ai[ii] >= 0) ext[d] = fmaxf(ext[d], fabsf(ri[ii][d]));
-    }
-  }
-  // one periodic image per candidate (taken against the first atom) is the
-  // nearest image for every i whenever extent + r_list + margin < L/2
-  const bool shift = ext[0] + incl + 0.02f < 0.5f * Lf[0] && ext[1] + incl + 0.02f < 0.5f * Lf[1] &&
-                     ext[2] + incl + 0.02f < 0.5f * Lf[2];
-  // i-side terms of |r_j - r_i|^2 = |r_j|^2 - 2 r_i.r_j + |r_i|^2 in the
-  // shifted frame (|r| < 25 A there, so the FP32 error of the expanded form
-  // stays below 1e-3 A^2, far inside the 0.01 A margin), held in scalar
-  // registers; a padding slot gets |r_i|^2 = 1e30 and never passes
-  float m2[kClus][3], nc2[kClus];
-#pragma unroll
-  for (int ii = 0; ii < kClus; ++ii) {
-    for (int d = 0; d < 3; ++d) m2[ii][d] = scalar(ai[ii] >= 0 ? -2.0f * ri[ii][d] : 0.0f);
-    nc2[ii] = scalar(ai[ii] >= 0 ? -__fmaf_rn(ri[ii][0], ri[ii][0], __fmaf_rn(ri[ii][1], ri[ii][1], ri[ii][2] * ri[ii][2]))
-                                 : -1.0e30f);
-  }
-  const int* cst = g.cellstart + (size_t)w * (g.ncell + 1);
-  unsigned* outL = g.lent + (size_t)item * 2 * cap;      // partners of atoms 0-3
-  unsigned* outH = outL + cap;                            // partners of atoms 4-7
+  const unsigned first = (unsigned)row * (unsigned)cap * 4u, limit = first + (unsigned)cap * 4u;
+  unsigned at = first;
   const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  const unsigned below = wave ? ~0u >> (32 - 8 * wave) : 0u;             // bytes of the waves before this one
   const int ncells = nC[0] * nC[1] * nC[2];
-  int countL = 0, countH = 0, par = 0;
+  int par = 0;
   // block index ci -> (c0, c1, c2) by float-reciprocal quotients with one
   // correction (exact for ci < 2^22, with the hardware reciprocal too); a
   // block coordinate lies in (-nf, 2nf)
@@ -467,13 +518,13 @@ __global__ __launch_bounds__(kBuildThreads) void k_build(const LegDev* legs, Blo
   const int n12 = nC[1] * nC[2];
   const float inv12 = __builtin_amdgcn_rcpf((float)n12), inv2 = __builtin_amdgcn_rcpf((float)nC[2]);
   auto wrapc = [nf](int c) { return c < 0 ? c + nf : (c >= nf ? c - nf : c); };
-  for (int cb = 0; cb < ncells; cb += kBuildThreads) {
-    const int ci = cb + tid;
+  for (int cb = 0; cb < ncells; cb += kThreads) {
+    const int cell = cb + tid;
     int s0 = 0, cnt = 0;
-    if (ci < ncells) {
-      int c0 = (int)((float)ci * inv12);
-      c0 += (ci - c0 * n12 < 0) ? -1 : (ci - c0 * n12 >= n12 ? 1 : 0);
-      const int rem = ci - c0 * n12;
+    if (cell < ncells) {
+      int c0 = (int)((float)cell * inv12);
+      c0 += (cell - c0 * n12 < 0) ? -1 : (cell - c0 * n12 >= n12 ? 1 : 0);
+      const int rem = cell - c0 * n12;
       int c1 = (int)((float)rem * inv2);
       c1 += (rem - c1 * nC[2] < 0) ? -1 : (rem - c1 * nC[2] >= nC[2] ? 1 : 0);
       const int C[3] = {r0[0] + c0, r0[1] + c1, r0[2] + rem - c1 * nC[2]};
@@ -499,7 +550,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_build(const LegDev* legs, Blo
         unsigned hc[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k)
-          hc[k] = g.hcell[((W0 + (k >> 2)) * nff + W1 + ((k >> 1) & 1)) * nff + W2 + (k & 1)];
+          hc[k] = hcell[((W0 + (k >> 2)) * nff + W1 + ((k >> 1) & 1)) * nff + W2 + (k & 1)];
         unsigned kmin = 0xffffffffu, kmax = 0u;
 #pragma unroll
         for (int k = 0; k < 8; ++k)
@@ -518,104 +569,170 @@ __global__ __launch_bounds__(kBuildThreads) void k_build(const LegDev* legs, Blo
       const int v = __shfl_up(inc, k, 64);
       if (lane >= k) inc += v;
     }
-    if (lane == 63) s_wsum[wave] = inc;
-    s_start[tid] = s0;
+    const unsigned long long held = __ballot(cnt > 0);
+    if (lane == 63) { s_wsum[wave] = inc; s_wblk[wave] = __popcll(held); }
     __syncthreads();
-    int woff = 0;
-    for (int k = 0; k < wave; ++k) woff += s_wsum[k];
-    int total = 0;
-    for (int k = 0; k < kBuildWaves; ++k) total += s_wsum[k];
-    const int pre_t = woff + inc - cnt;
-    s_pre[tid] = pre_t;
-    // candidates are taken kCellOf at a time: each block writes its index over
-    // its share of the window, then a candidate finds its block in one read
-    for (int T0 = 0; T0 < total; T0 += kCellOf) {
-    {
-      const int b0 = max(pre_t, T0), b1 = min(pre_t + cnt, T0 + kCellOf);
-      for (int q = b0; q < b1; ++q) s_cellof[q - T0] = (unsigned char)tid;
+    int pos = inc - cnt, blk = __popcll(held & lt), total = 0;
+    for (int k = 0; k < WAVES; ++k) {
+      if (k < wave) { pos += s_wsum[k]; blk += s_wblk[k]; }
+      total += s_wsum[k];
     }
-    __syncthreads();
-    const int T1 = min(total, T0 + kCellOf);
-    for (int t0 = T0; t0 < T1; t0 += kBuildThreads) {
-      const int t = t0 + tid;
-      unsigned mask = 0;
-      int s = 0;
-      if (t < T1) {
-        const int l = s_cellof[t - T0];
-        s = s_start[l] + (t - s_pre[l]);
-        const int a = perm[s];
-        const float4 rj = xq[s];
-        const float xj[3] = {rj.x, rj.y, rj.z};
-        {
+    total = __builtin_amdgcn_readfirstlane(total);
+    if (cnt > 0) s_delta[blk] = s0 - pos;
+    // candidate t belongs to the block whose number is the count of blocks
+    // that open at 1..t: bit t - 1 marks an opening at t, kTabOf at a time
+    int opened = 0;
+    for (int T0 = 0; T0 < total; T0 += kTabOf) {
+      for (int k = tid; k < kTabOf / 64; k += kThreads) s_bits[k] = 0ull;
+      __syncthreads();
+      if (cnt > 0 && pos > T0 && pos <= T0 + kTabOf)
+        atomicOr((unsigned*)s_bits + ((pos - 1 - T0) >> 5), 1u << ((pos - 1 - T0) & 31));
+      __syncthreads();
+      const int T1 = min(total, T0 + kTabOf);
+      // a lane's candidate of the step at t0, loaded a step ahead
+      int s, a;
+      f32x4 xj;
+      auto fetch = [&](int t0) {
+        unsigned long long mine = 0ull;
+        int op = opened;
+        for (int k = 0; k < WAVES; ++k) {
+          const unsigned long long v = s_bits[((t0 - T0) >> 6) + k];
+          const int ones = __popcll(v);
+          if (k < wave) op += ones;
+          if (k == wave) mine = v;
+          opened += ones;
+        }
+        const int t = t0 + tid;
+        const int blkno = __builtin_amdgcn_mbcnt_hi((unsigned)(mine >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mine, op));
+        const int v = t + s_delta[blkno];
+        s = t < T1 ? v : slot0;
+        a = *(gptr<int>)((gptr<char>)perm + 4u * (unsigned)s);
+        xj = *(gptr<f32x4>)((gptr<char>)xq + 16u * (unsigned)s);
+      };
+      fetch(T0);
+      for (int t0 = T0; t0 < T1; t0 += kThreads) {
+        const int tb = t0 + 64 * wave;                    // this wave's part
+        unsigned m[4] = {0u, 0u, 0u, 0u}, ent[4];
+        const int s_now = s, a_now = a;
+        const f32x4 xj_now = xj;
+        if (t0 + kThreads < T1) fetch(t0 + kThreads);
+        if (tb < T1) {
+          const int s = s_now, a = a_now;
+          const f32x4 xj = xj_now;
+          const bool in = tb + lane < T1;
+          // possibly an own or excluded atom?  (settled below)
+          const unsigned bit = (s_bloom[(a >> 5) & (kBloomWords - 1)] >> (a & 31)) & 1u;
+          unsigned long long hits = __ballot(bit) & __ballot(in);
+          spread_rows((unsigned)s << 8, ent);
           if (shift) {
-            float rj3[3];
+            float r[3];
             for (int d = 0; d < 3; ++d) {
-              const float v = xj[d] - xi[0][d];
-              rj3[d] = __fmaf_rn(-Lf[d], rintf(v * iLf[d]), v);
+              const float v = xj[d] - x0[d];
+              r[d] = __fmaf_rn(-Lf[d], rintf(v * iLf[d]), v);
             }
-            // |r_j|^2 - 2 r_i.r_j - (r_list + 0.01)^2 < -|r_i|^2
-            const float nthr = __fmaf_rn(rj3[0], rj3[0], __fmaf_rn(rj3[1], rj3[1], rj3[2] * rj3[2])) - inc2;
+            float thr = __fmaf_rn(r[0], r[0], __fmaf_rn(r[1], r[1], r[2] * r[2])) - inc2;
+            const bool ok = in && thr < kFar;
+            if (__ballot(!ok)) {                    // past the end, or a NaN position: in no list
+              asm volatile("");
+              for (int d = 0; d < 3; ++d) r[d] = ok ? r[d] : 0.f;
+              thr = ok ? thr : kFar;
+            }
+            float bm[4] = {r[0], r[1], r[2], thr};
+            transpose_rows(bm);
 #pragma unroll
-            for (int ii = kClus - 1; ii >= 0; --ii) {        // bit ii ends at position ii
-              const float q = __fmaf_rn(m2[ii][0], rj3[0], __fmaf_rn(m2[ii][1], rj3[1], __fmaf_rn(m2[ii][2], rj3[2], nthr)));
-              mask = 2u * mask + (q < nc2[ii] ? 1u : 0u);
+            for (int k = 0; k < 4; ++k) {
+              const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x4f32(am, bm[k], ci, 0, 0, 0);
+              unsigned v = __float_as_uint(d[3]) >> 31;           // bit r: atom r is in range (its sign)
+              v = __builtin_amdgcn_alignbit(v, __float_as_uint(d[2]), 31);
+              v = __builtin_amdgcn_alignbit(v, __float_as_uint(d[1]), 31);
+              m[k] = __builtin_amdgcn_alignbit(v, __float_as_uint(d[0]), 31);
             }
           } else {
-            // rare (small boxes, spread clusters): positions from LDS and no
-            // unrolling, so this path adds no registers to the common one
-#pragma unroll 1
-            for (int ii = 0; ii < kClus; ++ii) {
-              float dx = xj[0] - s_xi[ii][0], dy = xj[1] - s_xi[ii][1], dz = xj[2] - s_xi[ii][2];
-              dx -= Lf[0] * rintf(dx * iLf[0]);
-              dy -= Lf[1] * rintf(dy * iLf[1]);
-              dz -= Lf[2] * rintf(dz * iLf[2]);
-              const float d2 = (dx * dx + dy * dy) + dz * dz;
-              if (d2 < inc2 && ai[ii] >= 0) mask |= 1u << ii;
+            // small boxes and spread clusters: the nearest image per pair
+            unsigned mask = 0;
+#pragma unroll 4
+            for (int ii = 0; ii < 16; ++ii) {
+              const float4 p = s_xi[ii];
+              float dx = xj[0] - p.x, dy = xj[1] - p.y, dz = xj[2] - p.z;
+              dx = __fmaf_rn(-Lf[0], rintf(dx * iLf[0]), dx);
+              dy = __fmaf_rn(-Lf[1], rintf(dy * iLf[1]), dy);
+              dz = __fmaf_rn(-Lf[2], rintf(dz * iLf[2]), dz);
+              const float d2 = __fmaf_rn(dx, dx, __fmaf_rn(dy, dy, __fmaf_rn(dz, dz, p.w)));
+              mask |= d2 < inc2 ? 1u << ii : 0u;
             }
+            unsigned v[4];
+            spread_rows(in ? mask : 0u, v);
+            for (int k = 0; k < 4; ++k) m[k] = (v[k] >> (4 * row)) & 0xFu;
           }
-          const unsigned self = (unsigned)(s - c * kClus);       // the cluster's own atom: no i == j pair
-          if (self < (unsigned)kClus) mask &= ~(1u << self);
-          if (mask && ((s_bloom[(a >> 5) & 63] >> (a & 31)) & 1u)) {   // possibly excluded
-            for (int ii = 0; ii < kClus; ++ii) {
-              if (!((mask >> ii) & 1u)) continue;
-              bool ex = false;
-              for (int k = 0; k < s_nex[ii]; ++k) ex |= (s_ex[ii][k] == a);
-              if (ex) mask &= ~(1u << ii);
+          if (hits) {
+            // the pairs of these candidates that are an atom with itself or
+            // excluded: 16 bits over the pair's atoms
+            unsigned drop = 0;
+            do {
+              const int q = __builtin_ctzll(hits);
+              hits &= hits - 1;
+              const int aq = __builtin_amdgcn_readlane(a, q);
+              unsigned long long x = __ballot(ex[0] == aq) | __ballot(ex[1] == aq) | __ballot(own == aq);
+              x |= x >> 32;
+              drop = lane == q ? (unsigned)(x | x >> 16) & 0xFFFFu : drop;
+            } while (hits);
+            unsigned v[4];
+            spread_rows(drop, v);
+            for (int k = 0; k < 4; ++k) {
+              const unsigned x = (v[k] >> (4 * row)) & 0xFu;
+              m[k] &= ~x;
             }
           }
         }
+        // place of each entry: the four parts' flags in the four bytes of a
+        // word, summed along the row, then over the parts, then over the waves
+        unsigned f = 0;
+        for (int k = 0; k < 4; ++k) f |= min(m[k], 1u) << (8 * k);
+        unsigned sum = f;
+        sum += row_shr<1>(sum);
+        sum += row_shr<2>(sum);
+        sum += row_shr<4>(sum);
+        sum += row_shr<8>(sum);
+        unsigned tot = row_last(sum);
+        tot += tot << 8;
+        asm("" : "+v"(tot));                        // (else a multiplication, at a quarter of the rate)
+        tot += tot << 16;
+        asm("" : "+v"(tot));
+        const unsigned place = sum - f + (tot << 8);
+        unsigned o4 = at;
+        if (WAVES > 1) {
+          if (col == 0) ((unsigned char*)&s_wc[par][row])[wave] = (unsigned char)(tot >> 24);
+          __syncthreads();
+          const unsigned v = s_wc[par][row];
+          o4 += 4u * __builtin_amdgcn_sad_u8(v & below, 0u, 0u);
+          at += 4u * __builtin_amdgcn_sad_u8(v, 0u, 0u);
+          par ^= 1;
+        } else {
+          at += 4u * (tot >> 24);
+        }
+        if (tb < T1) {
+          unsigned p[4];
+          for (int k = 0; k < 4; ++k) p[k] = o4 + 4u * ((place >> (8 * k)) & 0xFFu);
+          if (__ballot(at > limit)) {               // past the capacity: counted, not stored
+            asm volatile("");                       // (a branch: not selects on the way of every step)
+            for (int k = 0; k < 4; ++k) m[k] = p[k] < limit ? m[k] : 0u;
+          }
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if (m[k]) *(__attribute__((address_space(1))) unsigned*)(lists + p[k]) = ent[k] | m[k];
+        }
       }
-      const unsigned mL = mask & 0xFu, mH = mask >> 4;
-      const unsigned long long bL = __ballot(mL != 0u), bH = __ballot(mH != 0u);
-      if (lane == 0) { s_wc[par][0][wave] = __popcll(bL); s_wc[par][1][wave] = __popcll(bH); }
-      __syncthreads();
-      int offL = countL, offH = countH;
-      for (int k = 0; k < wave; ++k) { offL += s_wc[par][0][k]; offH += s_wc[par][1][k]; }
-      for (int k = 0; k < kBuildWaves; ++k) { countL += s_wc[par][0][k]; countH += s_wc[par][1][k]; }
-      if (mL) {
-        const int pos = offL + __popcll(bL & lt);
-        if (pos < cap) outL[pos] = ((unsigned)s << 8) | mL;
-      }
-      if (mH) {
-        const int pos = offH + __popcll(bH & lt);
-        if (pos < cap) outH[pos] = ((unsigned)s << 8) | mH;
-      }
-      par ^= 1;
+      __syncthreads();                          // the table is rewritten next
     }
-    __syncthreads();                            // the window's table is rewritten next
-    }
-    __syncthreads();                            // the round's tables are rewritten next
+    __syncthreads();                            // the round's sums and blocks are rewritten next
   }
-  const int count = max(countL, countH);
-  if (count > cap) {
-    if (tid == 0) {
-      latch(g.err, kErrListCap, kSiteList, (w << 20) | max(s_ai[0], 0), g.leg_index);
+  if (wave == 0 && col == 0 && c + (row >> 1) < g.nclus) {
+    const int count = (int)((at - first) >> 2);
+    if (count > cap) {
+      latch(g.err, kErrListCap, kSiteList, (w << 20) | max(perm[slot0], 0), g.leg_index);
       atomicMax(g.need, count);
     }
-  }
-  if (tid == 0) {
-    g.lcount[2 * item] = min(countL, cap);
-    g.lcount[2 * item + 1] = min(countH, cap);
+    g.lcount[2 * item + row] = min(count, cap);
   }
 }
 
@@ -696,8 +813,9 @@ void launch_sort_pack(hipStream_t s, const LegDev* d, const LegHost* h, int nl) 
 
 void launch_lists(hipStream_t s, const LegDev* d, const LegHost* h, int nl) {
   BlockMap m;
-  const int nb = make_map(m, nl, [&](int i) { return h[i].W * h[i].nclus; });
-  if (nb) hipLaunchKernelGGL(k_build, dim3(nb), dim3(kBuildThreads), 0, s, d, m);
+  const int nb = make_map(m, nl, [&](int i) { return h[i].W * ((h[i].nclus + 1) / 2); });
+  if (nb > kFewPairs) hipLaunchKernelGGL(k_build<1>, dim3(nb), dim3(64), 0, s, d, m);
+  else if (nb) hipLaunchKernelGGL(k_build<4>, dim3(nb), dim3(256), 0, s, d, m);
 }
 
 void launch_build(hipStream_t s, const LegDev* d, const LegHost* h, int nl) {
