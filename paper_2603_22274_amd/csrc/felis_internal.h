@@ -19,6 +19,7 @@ constexpr int kMaxRadix = 8;        // FFT stages per axis
 constexpr int kMaxHrex = 256;       // most windows a leg may exchange among
 constexpr int kMaxFFT = 128;        // largest PME grid dimension (bases pack in 7 bits)
 constexpr int kClus = 8;            // atoms per i-cluster (pair kernel)
+constexpr unsigned kListPartial = 0x10u;   // list entry: its mask lacks an excluded pair or the atom itself
 
 constexpr double kKE = 332.06371;                 // kcal A / (mol e^2)
 constexpr double kBar = 1.0e-25 * 6.02214076e23 / 4184.0;   // 1 bar in kcal / (mol A^3)
@@ -157,7 +158,7 @@ struct LegDev {
   float4* bbhi;
   int* lcount;                          // [W][nclus][2] entries per half-cluster list
   unsigned* lent;                       // [W][nclus][2][cap]: list of the cluster's atoms 0-3 and of
-                                        // atoms 4-7 (slot << 8 | 4-bit mask over the half's atoms)
+                                        // atoms 4-7 (slot << 8 | kListPartial | 4-bit mask over the half's atoms)
   long long *frx, *fry, *frz;           // [W][n] reciprocal-space and bonded forces of the current MD step
   long long* grid64;                    // [2 npair][Ktot] u_kn ligand charge grids, fixed point
   float* phi;                           // [2 npair][PhiLines size] potential of each window (u_kn: of each frame's
@@ -263,6 +264,12 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ gptr<f32x4> as_global4(const float4* p) { return (gptr<f32x4>)p; }
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ gptr<f32x2> as_global2(const float2* p) { return (gptr<f32x2>)p; }
+
+// LDS written by a wave, then read by its other lanes (or the reverse)
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
 // the value of the lane whose index differs by 1 (2) within the quad
 __device__ __forceinline__ float quad_xor1(float v) {

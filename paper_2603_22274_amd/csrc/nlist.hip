@@ -680,6 +680,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 1 ? 6 : 5) void k_build(const 
             spread_rows(drop, v);
             for (int k = 0; k < 4; ++k) {
               const unsigned x = (v[k] >> (4 * row)) & 0xFu;
+              ent[k] |= (m[k] & x) ? kListPartial : 0u;
               m[k] &= ~x;
             }
           }

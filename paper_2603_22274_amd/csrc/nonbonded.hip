@@ -7,8 +7,8 @@
 // the ligand and 1 otherwise; Lorentz-Berthelot mixing; everything cut at r_c
 // (appendix B).  Real-space Coulomb is the Ewald direct term erfc(a r)/r.
 //
-// Pair kernel layout (gfx950, wave64): one wave per 8-atom i-cluster; the
-// cluster's i-atoms are wave-uniform (scalar registers).  The cluster's two
+// Pair kernel layout (gfx950, wave64): one wave per 8-atom i-cluster; a
+// half-cluster's i-atoms are wave-uniform (scalar registers).  The cluster's two
 // half-lists (partners of atoms 0-3, then of atoms 4-7) are swept in turn:
 // each lane takes one listed j-atom per step and interacts it with the half's
 // 4 i-atoms, so a j entry is loaded, decoded and imaged once for 4 pairs, and
@@ -17,6 +17,8 @@
 // is summed by one wave in a fixed order and written once: no atomics and no
 // cross-wave ordering.  FP32 arithmetic; energies summed in FP64 per lane and
 // combined in int64 fixed point.
+#include <type_traits>
+
 #include "felis_internal.h"
 
 #include "erfc_coeffs.h"
@@ -99,13 +101,48 @@ __device__ __forceinline__ float3 min_img(const BoxW& B, float dx, float dy, flo
   return make_float3(dx, dy, dz);
 }
 
-// The 8 i-atoms of a cluster, wave-uniform (held in scalar registers).
-struct ICluster {
-  float x[kClus], y[kClus], z[kClus], q[kClus], sig[kClus], eps[kClus], lig[kClus];
+// The 4 i-atoms of a half-cluster, wave-uniform (held in scalar registers).
+struct IHalf {
+  float x[4], y[4], z[4], q[4], sig[4], eps[4];
 };
 
 __device__ __forceinline__ float uniform(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+
+// Sums of four values over the wave, value k's in the 16 lanes of row k.  Half
+// the wave's exchange and adds go away with each of the first two steps, which
+// fold two values into one register; the steps pair lanes 32, 16, 8, 4, 2 and 1
+// apart, in the order (and so with the rounding) of wave_sum.
+__device__ __forceinline__ float wave_sum4(float v0, float v1, float v2, float v3) {
+  auto swap32 = [](float& a, float& b) {         // a's upper half with b's lower half
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+  };
+  auto swap16 = [](float& a, float& b) {         // a's odd rows with b's even rows
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+  };
+  swap32(v0, v2);
+  swap32(v1, v3);
+  float a = v0 + v2, b = v1 + v3;                // rows 0, 1: values 0 (1); rows 2, 3: values 2 (3)
+  swap16(a, b);
+  a += b;                                        // row k: value k
+  auto dpp = [](float v, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  a += dpp(a, std::integral_constant<int, 0x128>{});   // 8 lanes on within the row
+  a += dpp(a, std::integral_constant<int, 0x124>{});   // 4 (the row now repeats after 8)
+  a += quad_xor2(a);
+  a += quad_xor1(a);
+  return a;
+}
+
+// lane `src`'s value (src wave-uniform), in a scalar register
+__device__ __forceinline__ float lane_of(float v, int src) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src));
 }
 
 // a window's box edges held in scalar registers for a whole kernel
@@ -119,17 +156,38 @@ __device__ __forceinline__ BoxF box_f(const BoxW& B) {
   return b;
 }
 
+// The periodic image of a partner against a cluster, axis by axis and held in
+// scalar registers: partners' coordinates are wrapped into [0, L), so the one
+// nearest the cluster's first atom (at x0) is x - L for x > x0 + L/2 when x0 <
+// L/2, and x + L for x < x0 - L/2 otherwise; none is needed on an axis where the
+// cluster lies r_c inside both faces (every partner within r_c then has its
+// wrapped coordinate as its nearest image, and any other image only lengthens
+// the separation).
+struct Image {
+  float t[3];                               // x0 +- L/2
+};
+
+// A cluster's yes-or-no facts in one scalar register (a condition held across
+// the sweep would take a register pair each)
+constexpr int kFlagAxis = 0;                // + d: axis d needs the image
+constexpr int kFlagLow = 3;                 // + d: x0 < L/2
+constexpr int kFlagLig = 8;                 // + k: the half's atom k belongs to the ligand, in a softcore window
+constexpr int kFlagLJ = 16;                 // + k: atom k has LJ
+constexpr int kFlagSoft = 24;               // lambda_vdw < 1
+
+__device__ __forceinline__ float image(float x, float t, float L, bool low) {    // low: uniform
+  if (low) return x > t ? x - L : x;
+  return x < t ? x + L : x;
+}
+
 // Sweep a cluster's j-list: lane = listed j, unrolled loop over the cluster's
 // i-atoms.  IMG 1: the periodic image of j is chosen once against the
 // cluster's first atom (exact when r_c + cluster extent < L/2 on every axis);
-// IMG 2: none (the cluster lies r_c inside every face of the box, so every
-// partner within r_c has its wrapped coordinates as its nearest image, and
-// any other image only lengthens the separation); IMG 0: every (i, j) takes
-// its own minimum image.
-template <int ENERGY, int IMG, int HALF>
-__device__ __forceinline__ void sweep(const LegDev& g, const BoxF B, const ICluster& I, gptr<unsigned> ent, int cnt,
+// IMG 0: every (i, j) takes its own minimum image.
+template <int ENERGY, int IMG>
+__device__ __forceinline__ void sweep(const LegDev& g, const BoxF B, const Image& P, const IHalf& I, gptr<unsigned> ent, int cnt,
                                       gptr<f32x4> xq, gptr<f32x2> pr, int lane,
-                                      float lam_v, float a_sc, bool soft_window, float (&fx)[4],
+                                      float lam_v, float a_sc, int flags, float (&fx)[4],
                                       float (&fy)[4], float (&fz)[4], double& ec, double& el) {
   const float Lx = B.L[0], Ly = B.L[1], Lz = B.L[2];
   const float iLx = B.iL[0], iLy = B.iL[1], iLz = B.iL[2];
@@ -139,8 +197,8 @@ __device__ __forceinline__ void sweep(const LegDev& g, const BoxF B, const IClus
   const float kx2 = -alpha * alpha * 1.4426950408889634f;   // exp(-alpha^2 r^2) = 2^(kx2 r^2)
   // software pipeline: the entries two steps ahead and the partner data one
   // step ahead are in flight while a step computes
-  unsigned e_next = lane < cnt ? ent[lane] : 0u;          // slot 0 with an empty mask
-  unsigned e_next2 = 64 + lane < cnt ? ent[64 + lane] : 0u;
+  unsigned e_next = lane < cnt ? ent[lane] : kListPartial;          // slot 0 with an empty mask
+  unsigned e_next2 = 64 + lane < cnt ? ent[64 + lane] : kListPartial;
   f32x4 xj_next = xq[(int)(e_next >> 8)];
   f32x2 pj_next = pr[(int)(e_next >> 8)];
   for (int it = 0; it < cnt; it += 64) {
@@ -149,38 +207,48 @@ __device__ __forceinline__ void sweep(const LegDev& g, const BoxF B, const IClus
     const f32x2 pj = pj_next;
     e_next = e_next2;
     const int nidx = it + 128 + lane;
-    e_next2 = nidx < cnt ? ent[nidx] : 0u;
+    e_next2 = nidx < cnt ? ent[nidx] : kListPartial;
     xj_next = xq[(int)(e_next >> 8)];
     pj_next = pr[(int)(e_next >> 8)];
-    const float ligj = (__float_as_uint(pj.y) >> 31) ? 1.0f : 0.0f;
+    const bool ligj = __float_as_uint(pj.y) >> 31;
     float jx = xj.x, jy = xj.y, jz = xj.z;
-    if (IMG == 1) {
-      jx = fmaf(-Lx, rintf((jx - I.x[0]) * iLx), jx);
-      jy = fmaf(-Ly, rintf((jy - I.y[0]) * iLy), jy);
-      jz = fmaf(-Lz, rintf((jz - I.z[0]) * iLz), jz);
+    int fl = flags;
+    asm volatile("" : "+s"(fl));                          // tested afresh each step
+    if (IMG == 1) {                                       // uniform branches
+      if (fl & (1 << kFlagAxis)) { asm volatile(""); jx = image(jx, P.t[0], Lx, fl & (1 << kFlagLow)); }
+      if (fl & (2 << kFlagAxis)) { asm volatile(""); jy = image(jy, P.t[1], Ly, fl & (2 << kFlagLow)); }
+      if (fl & (4 << kFlagAxis)) { asm volatile(""); jz = image(jz, P.t[2], Lz, fl & (4 << kFlagLow)); }
+    }
+    // wave-uniform: does any lane hold an entry whose mask lacks a pair within
+    // reach (an excluded pair, the atom itself) or none at all (past the end)?
+    // Otherwise the masks say nothing that r < r_c does not: a pair missing
+    // from a mask for its distance was beyond r_list when the list was made.
+    // (An energy sum must not meet the padding atoms of the last cluster.)
+    unsigned long long listed[4] = {~0ull, ~0ull, ~0ull, ~0ull};      // lanes that list the pair, per i-atom
+    if (ENERGY || __ballot(e & kListPartial) != 0ull) {
+      asm volatile("");                                   // a branch, not a select in every step
+#pragma unroll
+      for (int k = 0; k < 4; ++k) listed[k] = __ballot((e >> k) & 1u);
     }
     // wave-uniform: does any listed j of this step belong to the ligand?
-    const bool jlig = soft_window && __ballot(ligj > 0.0f) != 0ull;
+    const bool jlig = (fl & (1 << kFlagSoft)) && __ballot(ligj) != 0ull;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const int ii = 4 * HALF + k;
-      float dx = jx - I.x[ii], dy = jy - I.y[ii], dz = jz - I.z[ii];
+      float dx = jx - I.x[k], dy = jy - I.y[k], dz = jz - I.z[k];
       if (IMG == 0) {
         dx = fmaf(-Lx, rintf(dx * iLx), dx);
         dy = fmaf(-Ly, rintf(dy * iLy), dy);
         dz = fmaf(-Lz, rintf(dz * iLz), dz);
       }
       const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-      // r^2 of a listed pair, 3e38 for an unlisted one (excluded, the atom
-      // itself or beyond r_list): one compare gives the in-range mask
-      const float r2m = ((e >> k) & 1u) ? r2 : 3.0e38f;
-      const bool in = r2m < rc2;
+      const unsigned long long in_lanes = __ballot(r2 < rc2) & listed[k];
       // wave-uniform: no lane's partner lies within r_c of this i-atom (the
       // list's entries are consecutive in the Hilbert order, so a wave's
       // partners are near one another and often all beyond r_c of one side
       // of the half-cluster); a skipped lane adds nothing, exactly as the
       // select below would.
-      if (__ballot(in) == 0ull) continue;
+      if (in_lanes == 0ull) continue;
+      const bool in = __builtin_amdgcn_inverse_ballot_w64(in_lanes);
       // lanes outside (in == false) may compute inf or NaN below: every
       // result they feed is dropped by the selects on `in`
       const float r2s = r2;
@@ -195,16 +263,16 @@ __device__ __forceinline__ void sweep(const LegDev& g, const BoxF B, const IClus
       for (int c = 1; c < FELIS_ERFC_NC; ++c) pt = fmaf(pt, t, felis_erfc_c[c]);
       pt *= t;
       const float ex = __builtin_amdgcn_exp2f(kx2 * r2s);
-      const float qq = I.q[ii] * xj.w;
+      const float qq = I.q[k] * xj.w;
       const float fc = qq * (ex * fmaf(pt, rinv, c2a)) * rinv2;
       float flj = 0.0f, elj = 0.0f;
-      if (I.eps[ii] == 0.0f) {
+      const bool ligi = fl & (1 << (kFlagLig + k));
+      if (!(fl & (1 << (kFlagLJ + k)))) {
         // wave-uniform: an i-atom without LJ (a water hydrogen) contributes
         // exactly zero LJ force and energy with every partner
-      } else if (const float sig = I.sig[ii] + pj.x, eps4 = I.eps[ii] * fabsf(pj.y);
-                 (jlig || (soft_window && I.lig[ii] > 0.0f)) &&
-                 __ballot(in && (I.lig[ii] + ligj) > 0.0f) != 0ull) {
-        const bool ligp = (I.lig[ii] + ligj) > 0.0f;
+      } else if (const float sig = I.sig[k] + pj.x, eps4 = I.eps[k] * fabsf(pj.y);
+                 (jlig || ligi) && __ballot(in && (ligi || ligj)) != 0ull) {
+        const bool ligp = ligi || ligj;
         const float lam = ligp ? lam_v : 1.0f;
         const float a = ligp ? a_sc : 0.0f;
         const float s2 = sig * sig;
@@ -250,9 +318,14 @@ __device__ __attribute__((noinline)) double excl_energy_fp64(const LegDev& g, co
   return -qq * erf(g.alphad * r) / r;
 }
 
+// Vector issue bounds it: 1.2 wave instructions per SIMD and 4 cycles (the most
+// seen here), some 38 a pair of a lane.  Hence masks only in the steps that need
+// them, the image only on the axes that need it, conditions as lane masks and
+// bits of one scalar register, and eight waves a SIMD (61 registers: one half's
+// i-atoms at a time).  20 windows of 40,000 atoms: 684 us with masks and images
+// in every step at five waves, 621 us.
 template <int ENERGY>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_pairs(const LegDev* legs,
-                                                                                      BlockMap map, int step) {
+__global__ __launch_bounds__(256, ENERGY ? 5 : 8) void k_pairs(const LegDev* legs, BlockMap map, int step) {
   const int leg = find_leg(map, blockIdx.x);
   const LegDev& g = legs[leg];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -267,65 +340,78 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   const float a_sc = g.lam[4 * w + 3];
   const bool soft_window = lam_v < 1.0f;
 
-  // i-atoms: images nearest the cluster's first atom (always a real atom:
-  // padding only follows the last atom), and the cluster's extent
-  ICluster I;
-  float ext[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-  for (int ii = 0; ii < kClus; ++ii) {
-    const f32x4 a = xq[c * kClus + ii];
-    const f32x2 p = pr[c * kClus + ii];
-    float v[3] = {uniform(a.x), uniform(a.y), uniform(a.z)};
-    if (ii > 0) {
-      const float r0[3] = {I.x[0], I.y[0], I.z[0]};
-      for (int d = 0; d < 3; ++d) {
-        v[d] = fmaf(-B.L[d], rintf((v[d] - r0[d]) * B.iL[d]), v[d]);
-        if (c * kClus + ii < g.n) ext[d] = fmaxf(ext[d], fabsf(v[d] - r0[d]));
-      }
-    }
-    I.x[ii] = v[0]; I.y[ii] = v[1]; I.z[ii] = v[2];
-    I.q[ii] = uniform(a.w);
-    I.sig[ii] = uniform(p.x);
-    I.eps[ii] = uniform(fabsf(p.y));
-    I.lig[ii] = uniform((__float_as_uint(p.y) >> 31) ? 1.0f : 0.0f);
+  // i-atoms, one in each of the first 8 lanes (repeated over the wave): images
+  // nearest the cluster's first atom (always a real atom: padding only follows
+  // the last atom), and the cluster's extent
+  const f32x4 ia = xq[c * kClus + (lane & 7)];
+  const f32x2 ip = pr[c * kClus + (lane & 7)];
+  const float r0[3] = {uniform(ia.x), uniform(ia.y), uniform(ia.z)};
+  float iv[3] = {ia.x, ia.y, ia.z}, ext[3];
+  for (int d = 0; d < 3; ++d) {
+    iv[d] = fmaf(-B.L[d], rintf((iv[d] - r0[d]) * B.iL[d]), iv[d]);
+    ext[d] = c * kClus + (lane & 7) < g.n ? fabsf(iv[d] - r0[d]) : 0.0f;
+    for (int k = 1; k < kClus; k <<= 1) ext[d] = fmaxf(ext[d], __shfl_xor(ext[d], k, 64));
+    ext[d] = uniform(ext[d]);
   }
+  // kept in LDS: in registers they would cost the sweep a wave of occupancy
+  __shared__ float s_i[4][6][kClus];
+  if (lane < kClus) {
+    s_i[wave][0][lane] = iv[0]; s_i[wave][1][lane] = iv[1]; s_i[wave][2][lane] = iv[2];
+    s_i[wave][3][lane] = ia.w; s_i[wave][4][lane] = ip.x; s_i[wave][5][lane] = fabsf(ip.y);
+  }
+  const unsigned ilig = soft_window ? (unsigned)__ballot(__float_as_uint(ip.y) >> 31) & 0xFFu : 0u;
+  const unsigned ilj = (unsigned)__ballot(ip.y != 0.0f) & 0xFFu;
+  int flags = soft_window ? 1 << kFlagSoft : 0;
   const float rc = sqrtf(g.rc2) + 0.01f;
   const bool shift = rc + ext[0] < 0.5f * B.L[0] && rc + ext[1] < 0.5f * B.L[1] && rc + ext[2] < 0.5f * B.L[2];
-  bool inside = shift;
+  Image P;
+#pragma unroll
   for (int d = 0; d < 3; ++d) {
-    const float x0 = d == 0 ? I.x[0] : (d == 1 ? I.y[0] : I.z[0]);
-    inside = inside && x0 - ext[d] - rc >= 0.0f && x0 + ext[d] + rc < B.L[d];
+    const float x0 = r0[d];
+    const bool inside = x0 - ext[d] - rc >= 0.0f && x0 + ext[d] + rc < B.L[d];
+    const bool low = x0 < 0.5f * B.L[d];
+    if (!inside) flags |= 1 << (kFlagAxis + d);
+    if (low) flags |= 1 << (kFlagLow + d);
+    P.t[d] = uniform(low ? x0 + 0.5f * B.L[d] : x0 - 0.5f * B.L[d]);
   }
-  const int img = inside ? 2 : (shift ? 1 : 0);
+  flags = __builtin_amdgcn_readfirstlane(flags);
   // the two half-cluster lists (partners of atoms 0-3, then of atoms 4-7);
   // each half's forces are reduced over the wave before the next half
   const gptr<unsigned> ent = as_global(g.lent + (size_t)item * 2 * g.cap);
   double ec = 0.0, el = 0.0;
   __shared__ float s_f[4][kClus][3];                  // per wave: the 8 atoms' pair forces
-#pragma unroll
+#pragma unroll 1
   for (int half = 0; half < 2; ++half) {
     float fx[4] = {0.f, 0.f, 0.f, 0.f}, fy[4] = {0.f, 0.f, 0.f, 0.f}, fz[4] = {0.f, 0.f, 0.f, 0.f};
     const gptr<unsigned> eh = ent + half * g.cap;
-    const int cnt = g.lcount[2 * item + half];
-#define FELIS_SWEEP(M, H) sweep<ENERGY, M, H>(g, B, I, eh, cnt, xq, pr, lane, lam_v, a_sc, soft_window, fx, fy, fz, ec, el)
-    if (half == 0) {
-      if (img == 2) FELIS_SWEEP(2, 0);
-      else if (img == 1) FELIS_SWEEP(1, 0);
-      else FELIS_SWEEP(0, 0);
-    } else {
-      if (img == 2) FELIS_SWEEP(2, 1);
-      else if (img == 1) FELIS_SWEEP(1, 1);
-      else FELIS_SWEEP(0, 1);
-    }
-#undef FELIS_SWEEP
+    const int cnt = __builtin_amdgcn_readfirstlane(g.lcount[2 * item + half]);
+    IHalf I;
+    {
+      wave_lds_fence();
+      float v[6];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float sx = wave_sum(fx[k]), sy = wave_sum(fy[k]), sz = wave_sum(fz[k]);
-      if (lane == 0) {
-        s_f[wave][4 * half + k][0] = sx;
-        s_f[wave][4 * half + k][1] = sy;
-        s_f[wave][4 * half + k][2] = sz;
+      for (int t = 0; t < 6; ++t) v[t] = s_i[wave][t][4 * half + (lane & 3)];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        I.x[k] = lane_of(v[0], k); I.y[k] = lane_of(v[1], k); I.z[k] = lane_of(v[2], k);
+        I.q[k] = lane_of(v[3], k);
+        I.sig[k] = lane_of(v[4], k);
+        I.eps[k] = lane_of(v[5], k);
       }
+    }
+    const int fl = __builtin_amdgcn_readfirstlane(flags | (int)(ilig >> (4 * half) & 0xFu) << kFlagLig |
+                                                  (int)(ilj >> (4 * half) & 0xFu) << kFlagLJ);
+    if (shift) sweep<ENERGY, 1>(g, B, P, I, eh, cnt, xq, pr, lane, lam_v, a_sc, fl, fx, fy, fz, ec, el);
+    else sweep<ENERGY, 0>(g, B, P, I, eh, cnt, xq, pr, lane, lam_v, a_sc, fl, fx, fy, fz, ec, el);
+    // atom k's sums end up in the 16 lanes of row k
+    const float sx = wave_sum4(fx[0], fx[1], fx[2], fx[3]);
+    const float sy = wave_sum4(fy[0], fy[1], fy[2], fy[3]);
+    const float sz = wave_sum4(fz[0], fz[1], fz[2], fz[3]);
+    if ((lane & 15) == 0) {
+      const int k = 4 * half + (lane >> 4);
+      s_f[wave][k][0] = sx;
+      s_f[wave][k][1] = sy;
+      s_f[wave][k][2] = sz;
     }
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -492,11 +578,6 @@ __device__ __forceinline__ void pair_energy_fp64(const EnergyLeg& g, const Energ
   const double s2 = sig * sig, s6 = s2 * s2 * s2;
   const double u = s6 * rcp_fp64(g.sc_alpha * (1.0 - lam) * s6 + r2 * r2 * r2);
   el += lam * 4.0 * eps * (u * u - u);
-}
-
-__device__ __forceinline__ void wave_lds_fence() {     // LDS written by a wave, then read by its other lanes
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
 }
 
 __global__ __launch_bounds__(256) void k_pair_energy(const LegDev* legs, BlockMap map) {

@@ -239,11 +239,6 @@ struct ScLane {                      // a lane's lambda_vdw value, its share of 
   double lam, asc, sum;
 };
 
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
 // lanes 0 .. KV groups - 1 take value lane % KV and every groups-th pair
 __device__ __forceinline__ ScLane sc_lane(const UknArgs& A, int lane) {
   ScLane L;
