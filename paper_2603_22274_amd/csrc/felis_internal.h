@@ -433,7 +433,7 @@ void launch_zero_energy(hipStream_t s, const LegDev* d, const LegHost* h, int nl
 void launch_finish_energy(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int c0, int c1);
 // ukn_mode: 0 the MD grids; u_kn int64 grids of 1 two frames per complex grid
 // or 2 one frame per grid (boxes from ubox)
-void launch_pme_fft(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int ukn_mode);
+void launch_pme_fft(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int ukn_mode, bool beside = false);
 void launch_hrex(hipStream_t s, const LegDev* d, const LegHost& h, const double* u, long long u_stride,
                  long long attempt, unsigned long long seed, int* accepted);
 int launch_ukn(hipStream_t s, hipStream_t side, hipEvent_t ev_fork, hipEvent_t ev_join, const LegDev* d, const LegHost& h, double sc_alpha, const double* lambdas,

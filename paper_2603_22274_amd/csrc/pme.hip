@@ -33,6 +33,16 @@ constexpr float kInvSqrtKE = 0.054876864878355476f;   // 1 / sqrt(KE): packed ch
 // MD step; planes up to 64 KB, e.g. 48^2, keep the whole-plane form)
 constexpr size_t kXYLdsCap = 65536;
 constexpr int kXYThreads = 512;               // threads per whole-plane workgroup: ~one butterfly each
+// Beside a pair kernel of more workgroups than the chip holds at once (2,048),
+// a workgroup of the transform gets a place only where pair workgroups end, and
+// those end one at a time: one wave and 64 registers on each of a CU's SIMDs.
+// Anything larger waits until no pair workgroup is left to take the place
+// first.  The *_beside forms fit (at most 256 threads, 64 registers).  With a
+// third of the pair workgroups or less in a second round the plain forms wait
+// little and end sooner: MD, us a pass, plain | beside: three served legs
+// 4,525 | 4,268, 20 windows of 7,540 atoms (4,720 pair workgroups) 1,524 | 1,472,
+// one window of 70,527 atoms (2,204) 763 | 772, 12 windows of 668 atoms 536 | 546.
+constexpr int kBesideBlocks = 3072;
 
 __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
   return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
@@ -241,7 +251,7 @@ __device__ __forceinline__ float2* fft_lines(float2* src, float2* dst, int n, co
 //       (frames) go to phi, each by itself in lines of 4 x 4 x 2 points for the
 //       gather.
 template <int AXIS, int FORM, int LINES>
-__global__ __launch_bounds__(256) void k_fft(const LegDev* legs, BlockMap map, int ukn) {
+__device__ __forceinline__ void line_pass(const LegDev* legs, const BlockMap& map, int ukn) {
   constexpr int MODE = FORM == 4 ? 0 : (FORM == 5 ? 3 : (FORM == 6 ? 1 : FORM));
   static_assert(FORM != 2 || LINES == 16, "a workgroup of the x pass transforms one flagged chunk");
   const int leg = find_leg(map, blockIdx.x);
@@ -419,6 +429,16 @@ __global__ __launch_bounds__(256) void k_fft(const LegDev* legs, BlockMap map, i
   }
 }
 
+template <int AXIS, int FORM, int LINES>
+__global__ __launch_bounds__(256) void k_fft(const LegDev* legs, BlockMap map, int ukn) {
+  line_pass<AXIS, FORM, LINES>(legs, map, ukn);
+}
+// in 64 registers, to run beside the pair kernel (see kBesideBlocks)
+template <int AXIS, int FORM, int LINES>
+__global__ __launch_bounds__(256, 8) void k_fft_beside(const LegDev* legs, BlockMap map, int ukn) {
+  line_pass<AXIS, FORM, LINES>(legs, map, ukn);
+}
+
 // One Stockham stage of radix R over nl lines held as buf[e * nl + b].
 template <int R>
 __device__ __forceinline__ void stage_nl(const float2* src, float2* dst, int n, int Ns, const FastDiv& dnl,
@@ -475,7 +495,7 @@ __device__ __forceinline__ float2* fft_lines_nl(float2* src, float2* dst, int n,
 // count the scatter into line order and the transpose hit one LDS bank with
 // every lane (96 lines: a stride of 192 dwords).
 template <bool INVERSE>
-__global__ __launch_bounds__(kXYThreads) void k_fft_xy(const LegDev* legs, BlockMap map) {
+__device__ __forceinline__ void plane_pass(const LegDev* legs, const BlockMap& map) {
   const int leg = find_leg(map, blockIdx.x);
   const LegDev& g = legs[leg];
   const int Kx = g.K[0], Ky = g.K[1], Kz = g.K[2];
@@ -533,6 +553,15 @@ __global__ __launch_bounds__(kXYThreads) void k_fft_xy(const LegDev* legs, Block
     const int y = dKx.div(idx), x = idx - y * Kx;
     cg[idx] = r[y * nly + x];                                       // [y][x] = grid order
   }
+}
+
+template <bool INVERSE>
+__global__ __launch_bounds__(kXYThreads) void k_fft_xy(const LegDev* legs, BlockMap map) {
+  plane_pass<INVERSE>(legs, map);
+}
+template <bool INVERSE>
+__global__ __launch_bounds__(256, 8) void k_fft_xy_beside(const LegDev* legs, BlockMap map) {
+  plane_pass<INVERSE>(legs, map);
 }
 
 __device__ __forceinline__ void bspline4(float f, float* w, float* dw) {
@@ -807,9 +836,18 @@ __device__ __forceinline__ unsigned brick_offsets(int b, int K, int P0, int size
 // atom (one z plane each): no wave waits for another before the brick is
 // written, where k_spread has four barriers a round.
 // 42 windows of 70,527 atoms on 96^3: 249 us alone, k_spread 345 us.
-__global__ __launch_bounds__(256) void k_spread_wide(const LegDev* legs, BlockMap map) {
+struct WideLds {
+  static constexpr int PL = kWide * kWide + 4;   // plane stride: a quad's four planes in different banks
+  float4 at[4][kSpreadList];                     // accepted atoms: stencil offsets, charge
+  uint2 of[4][kSpreadList];                      // their brick offsets: x | z's first two << 20, y | z's last two << 20
+  int2 rng[kSpreadRanges];                       // first slot and count of a candidate range
+  int tile[kWide * PL];
+  int nr[4];
+};
+
+__global__ __launch_bounds__(256, 8) void k_spread_wide(const LegDev* legs, BlockMap map) {
   constexpr int BX = kWide, BY = kWide, BZ = kWide;
-  constexpr int PL = BX * BY + 4;                // plane stride: a quad's four planes in different banks
+  constexpr int PL = WideLds::PL;
   const int leg = find_leg(map, blockIdx.x);
   const LegDev& g = legs[leg];
   // grid sizes in scalar registers (otherwise reloaded from memory inside the loops)
@@ -828,11 +866,9 @@ __global__ __launch_bounds__(256) void k_spread_wide(const LegDev* legs, BlockMa
   const int P0[3] = {bx * BX, by * BY, bz * BZ};
   const int size[3] = {min(BX, K[0] - P0[0]), min(BY, K[1] - P0[1]), min(BZ, K[2] - P0[2])};
 
-  __shared__ int tile[BZ * PL];
-  __shared__ int2 s_rng[kSpreadRanges];          // first slot and count of a candidate range
-  __shared__ int s_nr[4];
-  __shared__ float4 s_at[4][kSpreadList];        // accepted atoms: stencil offsets, charge
-  __shared__ uint2 s_of[4][kSpreadList];         // their brick offsets: x | z's first two << 20, y | z's last two << 20
+  extern __shared__ __attribute__((aligned(16))) char wide_smem[];
+  WideLds& S = *reinterpret_cast<WideLds*>(wide_smem);
+  int* const tile = S.tile;
   for (int e = tid; e < BZ * PL; e += 256) tile[e] = 0;
 
   // candidate blocks of 2 x 2 x 2 fine cells per axis
@@ -858,8 +894,8 @@ __global__ __launch_bounds__(256) void k_spread_wide(const LegDev* legs, BlockMa
   int na = 0;                                    // this wave's listed atoms
   auto add = [&](int first, int count) {
     for (int i = lane >> 2; i < count; i += 16) {
-      const float4 A = s_at[wave][first + i];
-      const uint2 of = s_of[wave][first + i];
+      const float4 A = S.at[wave][first + i];
+      const uint2 of = S.of[wave][first + i];
       const int iz = lane & 3;
       const unsigned oz = ((iz < 2 ? of.x : of.y) >> (20 + 5 * (iz & 1))) & 31u;
       if (oz == 31u) continue;
@@ -913,18 +949,18 @@ __global__ __launch_bounds__(256) void k_spread_wide(const LegDev* legs, BlockMa
     }
     // the ranges that hold atoms, in order
     const unsigned long long some = __ballot(cnt > 0);
-    if (lane == 0) s_nr[wave] = __popcll(some);
+    if (lane == 0) S.nr[wave] = __popcll(some);
     __syncthreads();                             // (also: the tile is cleared, the last ranges are read)
     int at = __popcll(some & lt), nr = 0;
     for (int k = 0; k < 4; ++k) {
-      if (k < wave) at += s_nr[k];
-      nr += s_nr[k];
+      if (k < wave) at += S.nr[k];
+      nr += S.nr[k];
     }
-    if (cnt > 0) s_rng[at] = make_int2(s0, cnt);
+    if (cnt > 0) S.rng[at] = make_int2(s0, cnt);
     __syncthreads();
     for (int q = 4 * wave; q < nr; q += 16) {    // four ranges a wave, 16 lanes each
       const int qi = q + (lane >> 4);
-      const int2 rg = qi < nr ? s_rng[qi] : make_int2(0, 0);
+      const int2 rg = qi < nr ? S.rng[qi] : make_int2(0, 0);
       for (int j = lane & 15; __ballot(j < rg.y) != 0ull; j += 16) {
         bool in = j < rg.y;
         const int slot = in ? rg.x + j : 0;
@@ -940,8 +976,8 @@ __global__ __launch_bounds__(256) void k_spread_wide(const LegDev* legs, BlockMa
         if (in) {
           const int k = na + __popcll(m & lt);
           // the window's charge (packed times sqrt(KE))
-          s_at[wave][k] = make_float4(st.x, st.y, st.z, xq[slot].w * kInvSqrtKE);
-          s_of[wave][k] = make_uint2(mx | (mz & 0x3FFu) << 20, my | (mz >> 10) << 20);
+          S.at[wave][k] = make_float4(st.x, st.y, st.z, xq[slot].w * kInvSqrtKE);
+          S.of[wave][k] = make_uint2(mx | (mz & 0x3FFu) << 20, my | (mz >> 10) << 20);
         }
         na += __popcll(m);
         wave_lds_fence();
@@ -1085,8 +1121,12 @@ __global__ __launch_bounds__(256) void k_gather(const LegDev* legs, BlockMap map
 
 inline int blocks_for(long long items, int per) { return (int)((items + per - 1) / per); }
 
-template <int AXIS, int MODE, int LINES>
+template <int AXIS, int MODE, int LINES, bool BESIDE = false>
 void fft_launch(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int ukn) {
+  constexpr auto kernel = [] {
+    if constexpr (BESIDE) return &k_fft_beside<AXIS, MODE, LINES>;
+    else return &k_fft<AXIS, MODE, LINES>;
+  }();
   BlockMap m;
   int nmax = 0;
   const int nb = make_map(m, nl, [&](int i) {
@@ -1099,12 +1139,12 @@ void fft_launch(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int uk
   if (lds > 65536) {
     // above 64 KB a kernel must opt in (128-point lines of 32: 66.5 KB);
     // once per instantiation, within the device's per-workgroup limit
-    static const bool opted = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_fft<AXIS, MODE, LINES>),
+    static const bool opted = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                   hipFuncAttributeMaxDynamicSharedMemorySize,
                                                   (int)(2 * 128 * LINES + 128) * (int)sizeof(float2)) == hipSuccess;
     if (!opted) (void)hipGetLastError();
   }
-  if (nb) hipLaunchKernelGGL((k_fft<AXIS, MODE, LINES>), dim3(nb), dim3(256), lds, s, d, m, ukn);
+  if (nb) hipLaunchKernelGGL(kernel, dim3(nb), dim3(256), lds, s, d, m, ukn);
 }
 
 // 32 lines per workgroup read and write 256-byte runs on the y and z passes
@@ -1116,15 +1156,17 @@ void fft_launch(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int uk
 constexpr long long kFftWideBlocks = 4096;
 
 template <int AXIS, int MODE>
-void fft_pass(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int ukn) {
+void fft_pass(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool beside) {
   long long wide = 0;
   for (int i = 0; i < nl; ++i) {
     const int inner = (AXIS == 0) ? h[i].K[1] : h[i].K[0];
     const int outer = (AXIS == 2) ? h[i].K[1] : h[i].K[2];
     wide += (long long)h[i].npair * outer * ((inner + 31) / 32);
   }
-  if (wide >= kFftWideBlocks) fft_launch<AXIS, MODE, 32>(s, d, h, nl, ukn);
-  else fft_launch<AXIS, MODE, 16>(s, d, h, nl, ukn);
+  if (wide >= kFftWideBlocks)
+    beside ? fft_launch<AXIS, MODE, 32, true>(s, d, h, nl, 0) : fft_launch<AXIS, MODE, 32>(s, d, h, nl, 0);
+  else
+    beside ? fft_launch<AXIS, MODE, 16, true>(s, d, h, nl, 0) : fft_launch<AXIS, MODE, 16>(s, d, h, nl, 0);
 }
 
 }  // namespace
@@ -1142,6 +1184,10 @@ size_t plane_lds_limit() {
     if (lim > 65536 &&
         (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_fft_xy<false>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lim) != hipSuccess ||
+         hipFuncSetAttribute(reinterpret_cast<const void*>(&k_fft_xy_beside<false>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lim) != hipSuccess ||
+         hipFuncSetAttribute(reinterpret_cast<const void*>(&k_fft_xy_beside<true>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lim) != hipSuccess ||
          hipFuncSetAttribute(reinterpret_cast<const void*>(&k_fft_xy<true>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lim) != hipSuccess)) {
       (void)hipGetLastError();
@@ -1152,7 +1198,7 @@ size_t plane_lds_limit() {
   return limit;
 }
 
-void launch_pme_fft(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int ukn_mode) {
+void launch_pme_fft(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int ukn_mode, bool beside) {
   const bool from_int64 = ukn_mode != 0;
   int plane = 0, kxy = 0;
   for (int i = 0; i < nl; ++i) {
@@ -1163,9 +1209,11 @@ void launch_pme_fft(hipStream_t s, const LegDev* d, const LegHost* h, int nl, in
   if (!from_int64 && lds <= std::min(plane_lds_limit(), kXYLdsCap)) {   // whole x-y planes in LDS
     BlockMap m;
     const int nb = make_map(m, nl, [&](int i) { return h[i].npair * h[i].K[2]; });
-    if (nb) hipLaunchKernelGGL(k_fft_xy<false>, dim3(nb), dim3(kXYThreads), lds, s, d, m);
-    fft_pass<2, 3>(s, d, h, nl, 0);
-    if (nb) hipLaunchKernelGGL(k_fft_xy<true>, dim3(nb), dim3(kXYThreads), lds, s, d, m);
+    if (!nb) return;
+    const int threads = beside ? 256 : kXYThreads;
+    hipLaunchKernelGGL(beside ? &k_fft_xy_beside<false> : &k_fft_xy<false>, dim3(nb), dim3(threads), lds, s, d, m);
+    fft_pass<2, 3>(s, d, h, nl, beside);
+    hipLaunchKernelGGL(beside ? &k_fft_xy_beside<true> : &k_fft_xy<true>, dim3(nb), dim3(threads), lds, s, d, m);
     return;
   }
   if (from_int64) {                             // (16 lines per workgroup, as the flags count rows)
@@ -1176,11 +1224,11 @@ void launch_pme_fft(hipStream_t s, const LegDev* d, const LegHost* h, int nl, in
     fft_launch<0, 6, 16>(s, d, h, nl, ukn_mode);
     return;
   }
-  fft_pass<0, 0>(s, d, h, nl, 0);
-  fft_pass<1, 0>(s, d, h, nl, 0);
-  fft_pass<2, 3>(s, d, h, nl, 0);
-  fft_pass<1, 1>(s, d, h, nl, 0);
-  fft_pass<0, 6>(s, d, h, nl, 0);
+  fft_pass<0, 0>(s, d, h, nl, beside);
+  fft_pass<1, 0>(s, d, h, nl, beside);
+  fft_pass<2, 3>(s, d, h, nl, beside);
+  fft_pass<1, 1>(s, d, h, nl, beside);
+  fft_pass<0, 6>(s, d, h, nl, beside);
 }
 
 void launch_pme(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool energy, bool step_forces) {
@@ -1193,12 +1241,15 @@ void launch_pme(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool e
   int nb = bricks(kWide, kWide, kWide);
   if (!nb) return;
   if (nb >= kWideBlocks) {
-    hipLaunchKernelGGL(k_spread_wide, dim3(nb), dim3(256), 0, s, d, m);
+    hipLaunchKernelGGL(k_spread_wide, dim3(nb), dim3(256), sizeof(WideLds), s, d, m);
   } else {
     nb = bricks(kBX, kBY, kBZ);
     hipLaunchKernelGGL(k_spread, dim3(nb), dim3(256), 0, s, d, m);
   }
-  launch_pme_fft(s, d, h, nl, 0);
+  // (forces of a step are taken on the side stream, beside the pair kernel)
+  long long pair_blocks = 0;
+  for (int i = 0; i < nl; ++i) pair_blocks += ((long long)h[i].W * h[i].nclus + 3) / 4;
+  launch_pme_fft(s, d, h, nl, 0, step_forces && pair_blocks >= kBesideBlocks);
   nb = make_map(m, nl, [&](int i) { return h[i].W * blocks_for((long long)h[i].npad, 64); });
   if (energy && step_forces) hipLaunchKernelGGL((k_gather<true, true>), dim3(nb), dim3(256), 0, s, d, m);
   else if (energy) hipLaunchKernelGGL((k_gather<true, false>), dim3(nb), dim3(256), 0, s, d, m);

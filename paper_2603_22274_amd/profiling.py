@@ -211,6 +211,10 @@ def counters(pmc_dir, kernels):
 
 _CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), 'csrc')
 PAIR_SOURCES = ('nonbonded.hip', 'erfc_coeffs.h', 'felis_internal.h')
+# passes of an MD step's transform, by itself and beside a large pair kernel
+FFT_KERNELS = tuple(f'k_fft{b}{a}' for b in ('', '_beside')
+                    for a in ('<0, 0, 32>', '<1, 0, 32>', '<2, 3, 32>', '<1, 1, 32>', '<0, 6, 32>')) + (
+    'k_fft_xy<false>', 'k_fft_xy<true>', 'k_fft_xy_beside<false>', 'k_fft_xy_beside<true>')
 WORKLOADS = {
     'complex42': ("42-window complex leg (70527 atoms, 96^3 grid)",
                   "python -u <repo>/bench.py --workload complex42 --steps 2 --warmup 0 --md 10 --equil 20 "
@@ -274,9 +278,7 @@ def write_profiles(out_dir, prof_dir, workload='complex42'):
     npair = (W + 1) // 2
     alg = {kernel: 48 * W * N,
            'k_spread': W * (32 * N + 4 * K3),                 # stencils + charges in, own grid component out
-           'k_fft_xy<false>': npair * K3 * 16, 'k_fft<0, 0, 32>': npair * K3 * 16, 'k_fft<1, 0, 32>': npair * K3 * 16,
-           'k_fft<2, 3, 32>': npair * K3 * 16, 'k_fft<1, 1, 32>': npair * K3 * 16, 'k_fft<0, 1, 32>': npair * K3 * 16,
-           'k_fft_xy<true>': npair * K3 * 16,
+           **{k: npair * K3 * 16 for k in FFT_KERNELS},
            'k_gather<false, true>': W * (4 * K3 + 56 * N),    # own grid component, stencils + charges, forces
            'k_integrate': W * N * 76, 'k_pack<true>': W * N * 48, 'k_build': None}
     txt += ["", "Every main kernel of the MD step (same two passes, same scaling; MB per launch):",
@@ -298,9 +300,7 @@ def write_profiles(out_dir, prof_dir, workload='complex42'):
         fh.write("\n".join(txt) + "\n")
     # per-axis FFT passes of the step: 32 lines per workgroup (the u_kn passes,
     # with 16 lines and a larger grid, are other launches)
-    ks = [kernel, 'k_build', 'k_spread', 'k_gather<false, true>', 'k_fft_xy<false>', 'k_fft<0, 0, 32>',
-          'k_fft<1, 0, 32>', 'k_fft<2, 3, 32>', 'k_fft<1, 1, 32>', 'k_fft<0, 1, 32>', 'k_fft_xy<true>', 'k_integrate',
-          'k_pack<true>']
+    ks = [kernel, 'k_build', 'k_spread', 'k_gather<false, true>', *FFT_KERNELS, 'k_integrate', 'k_pack<true>']
     A = counters(pre + 'A', ks)
     B = counters(pre + 'B', ks)
     lines = [f"VALU counters per dispatch, bench.py workload ({desc}), MI355X.",
