@@ -268,6 +268,7 @@ __global__ __launch_bounds__(1024) void k_check_sort(const LegDev* legs, BlockMa
   __shared__ int s_flag;
   const size_t o = (size_t)w * g.n;
   float m = 0.f;
+  const float limit2 = skin_threshold2(g, w);    // (loaded beside the displacements)
   force |= g.rbforce[w];                         // a box change (barostat) since the last build
   if (FROM_WORD) {
     if (g.units < 64) {
@@ -291,16 +292,18 @@ __global__ __launch_bounds__(1024) void k_check_sort(const LegDev* legs, BlockMa
   if (tid == 0) {
     float r = s_red[0];
     for (int k = 1; k < (int)(blockDim.x >> 6); ++k) r = fmaxf(r, s_red[k]);
-    const int f = (force || !(r <= skin_threshold2(g, w))) ? 1 : 0;
+    s_flag = (force || !(r <= limit2)) ? 1 : 0;
+  }
+  __syncthreads();
+  const int f = s_flag;                           // uniform over the block
+  if (tid == 0) {
     g.flag[w] = f;
     g.nbuild[w] += f;
     g.maxdisp[w] = 0u;
     g.rbforce[w] = 0;
     if (f) g.skin_used[w] = 0.f;
-    s_flag = f;
   }
-  __syncthreads();
-  if (!s_flag) return;                            // uniform over the block
+  if (!f) return;
 
   const int nc = g.ncell, n = g.n, nf = 1 << g.nbits;
   const float bL[3] = {g.box[w].Lf[0], g.box[w].Lf[1], g.box[w].Lf[2]};
@@ -354,18 +357,16 @@ __global__ __launch_bounds__(1024) void k_check_sort(const LegDev* legs, BlockMa
   __syncthreads();
   for (int a = tid; a < n; a += blockDim.x) s_perm[atomicAdd(&s_cur[s_code[a]], 1)] = a;
   __syncthreads();
-  for (int c = tid; c < nc; c += blockDim.x) {    // index order within each cell
-    const int b0 = s_st[c], b1 = s_st[c + 1];
-    for (int q = b0 + 1; q < b1; ++q) {
-      const int v = s_perm[q];
-      int t = q - 1;
-      while (t >= b0 && s_perm[t] > v) { s_perm[t + 1] = s_perm[t]; --t; }
-      s_perm[t + 1] = v;
-    }
-  }
-  __syncthreads();
+  // index order within each cell: an atom's place is the count of smaller
+  // indices in its cell
   int* p = g.perm + (size_t)w * g.npad;
-  for (int q = tid; q < g.npad; q += blockDim.x) p[q] = q < n ? s_perm[q] : -1;
+  for (int a = tid; a < n; a += blockDim.x) {
+    const int c = s_code[a], b0 = s_st[c], b1 = s_st[c + 1];
+    int q = b0;
+    for (int t = b0; t < b1; ++t) q += s_perm[t] < a ? 1 : 0;
+    p[q] = a;
+  }
+  for (int q = n + tid; q < g.npad; q += blockDim.x) p[q] = -1;
 }
 
 bool sort_in_lds(const LegHost& h) { return h.ncell <= kSortCells && h.n <= kSortAtoms; }
