@@ -50,3 +50,33 @@ def test_pairs_equal_the_canonical_list(n, box, kind, windows):
         assert got.shape == ref.shape and np.array_equal(got, ref), (w, got.shape, ref.shape)
     torch.cuda.synchronize()
     ctx.close()
+
+
+@pytest.mark.parametrize('n,box', [(1200, (30.0, 30.0, 30.0)), (900, (90.0, 80.0, 85.0)), (8192, (90.0, 80.0, 85.0)),
+                                   (12289, (44.0, 60.0, 52.0)), (10241, (95.0, 80.0, 85.0))])
+def test_one_atom_beyond_half_the_skin_rebuilds_its_window(n, box):
+    """The check of a call's first positions, for sizes on either side of its forms: the last atom, the first
+    and one in the middle, each in a window of its own."""
+    from paper_2603_22274_amd import felis
+    s = _system(n, box, 'even', windows=4)
+    ctx = felis.Context(0)
+    leg = felis.Leg(ctx, s, list_cap=4096)
+    felis.build_nlist(ctx, [leg], force=True)
+    ctx.device_check()
+    built = felis.leg_rebuilds(ctx, leg)
+    x = leg.x.view(4, n)
+    for w, a in enumerate((n - 1, 0, n // 2)):
+        x[w, a] += 0.499 * s.skin
+    felis.build_nlist(ctx, [leg])
+    assert np.array_equal(felis.leg_rebuilds(ctx, leg), built)
+    for w, a in enumerate((n - 1, 0, n // 2)):
+        x[w, a] += 0.002 * s.skin
+    felis.build_nlist(ctx, [leg])
+    assert np.array_equal(felis.leg_rebuilds(ctx, leg) - built, [1, 1, 1, 0])
+    felis.build_nlist(ctx, [leg])
+    assert np.array_equal(felis.leg_rebuilds(ctx, leg) - built, [1, 1, 1, 0])
+    pos = torch.stack([leg.x.view(4, n), leg.y.view(4, n), leg.z.view(4, n)], -1).cpu().numpy()
+    ref = opairs.neighbor_pairs_tree(pos[0], s.box, s, s.r_list)
+    assert np.array_equal(felis.nlist_export_pairs(ctx, leg, 0), ref)
+    ctx.device_check()
+    ctx.close()
