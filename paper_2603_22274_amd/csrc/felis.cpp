@@ -374,6 +374,13 @@ int prepare(felis_ctx* c, const felis_leg* legs, int n_legs, std::vector<LegHost
   return FELIS_OK;
 }
 
+// Fewest pair workgroups for which the gather ends before the pair kernel.
+// MD, us a pass, bonded forces behind the gather | behind the pairs: 12 windows
+// of 668 atoms (252 workgroups) 490 | 463, one window of 70,527 atoms (2,204)
+// 647 | 628, NPT, 20 windows of 7,540 (4,720) 1,735 | 1,706, three served legs
+// (19,500) 4,262 | 4,341, 42 windows of 70,527 (92,600) 11,770 | 12,070.
+constexpr long long kLongPairs = 8192;
+
 // Records an event for timer t when profiling is on (start when stop == false).
 void mark(felis_ctx* c, int t, bool stop, hipStream_t s) {
   if (!((c->prof >> t) & 1)) return;
@@ -882,13 +889,17 @@ int felis_step(felis_ctx* c, felis_leg* legs, int n_legs, int n_steps, double dt
     mark(c, FELIS_PROF_PME, false, c->side);
     launch_pme(c->side, c->d_legs, hs.data(), n_legs, false, true);
     mark(c, FELIS_PROF_PME, true, c->side);
-    launch_bonded_step(c->side, c->d_legs, hs.data(), n_legs);
+    // the bonded forces go to the stream that ends first: behind the pair kernel,
+    // or behind the gather where the pair kernel is long
+    const bool after_pairs = pair_blocks(hs.data(), n_legs) < kLongPairs;
+    if (!after_pairs) launch_bonded_step(c->side, c->d_legs, hs.data(), n_legs, false);
     (void)hipEventRecord(c->ev_join, c->side);
     launch_lists(c->stream, c->d_legs, hs.data(), n_legs);
     mark(c, FELIS_PROF_NLIST, true);       // the build stage also packs the sorted coordinates
     mark(c, FELIS_PROF_PAIRS, false);
     launch_pairs(c->stream, c->d_legs, hs.data(), n_legs, 0, true);
     mark(c, FELIS_PROF_PAIRS, true);
+    if (after_pairs) launch_bonded_step(c->stream, c->d_legs, hs.data(), n_legs, true);
     (void)hipStreamWaitEvent(c->stream, c->ev_join, 0);
     mark(c, FELIS_PROF_INTEGRATE, false);
     launch_integrate(c->stream, c->d_legs, hs.data(), n_legs, step.data(), seed.data(), (float)dt,

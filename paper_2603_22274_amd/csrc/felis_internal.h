@@ -395,6 +395,13 @@ struct LegHost {
   int nmol;                             // > 0 only for legs with a barostat
 };
 
+// workgroups of the pair kernel: four clusters each
+inline long long pair_blocks(const LegHost* h, int nl) {
+  long long nb = 0;
+  for (int i = 0; i < nl; ++i) nb += ((long long)h[i].W * h[i].nclus + 3) / 4;
+  return nb;
+}
+
 // One barostat attempt for a batch: which legs move, their attempt index,
 // noise key and pressure (kcal / (mol A^3))
 struct BaroArgs {
@@ -424,8 +431,9 @@ void launch_bonded(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int
 // step_forces: the gather stores each atom's force in frx/fry/frz (read by the
 // integrator) instead of adding it to fx/fy/fz
 void launch_pme(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool energy, bool step_forces = false);
-// the step's bonded forces, added to frx/fry/frz (after the gather has stored there)
-void launch_bonded_step(hipStream_t s, const LegDev* d, const LegHost* h, int nl);
+// the step's bonded forces, added to fx/fy/fz (after_pairs: after the pair kernel
+// has stored there) or to frx/fry/frz (after the gather has)
+void launch_bonded_step(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool after_pairs);
 void launch_integrate(hipStream_t s, const LegDev* d, const LegHost* h, int nl,
                       const long long* step, const unsigned long long* seed, float dt,
                       float temperature, float gamma);

@@ -118,12 +118,12 @@ __device__ __forceinline__ v3 bonded_force(const LegDev& g, int w, int a) {
 }
 
 // items: window x bonded atom (any atom with a bond, a torsion or an anchor):
-// adds its bonded terms to its reciprocal-space force, after the gather has
-// stored that.  A kernel of its own, ahead of the integrator: the partners'
+// adds its bonded terms to its pair force or its reciprocal-space force,
+// after that has been stored.  A kernel of its own, ahead of the integrator: the partners'
 // positions must be those of the step's start, and the integrator overwrites
 // them (summed there, an atom whose partner's wave had already stored saw the
 // new position).
-__global__ __launch_bounds__(256) void k_bonded_step(const LegDev* legs, BlockMap map) {
+__global__ __launch_bounds__(256) void k_bonded_step(const LegDev* legs, BlockMap map, int after_pairs) {
   const int leg = find_leg(map, blockIdx.x);
   const LegDev& g = legs[leg];
   const long long i = (long long)(blockIdx.x - map.start[leg]) * blockDim.x + threadIdx.x;
@@ -141,9 +141,10 @@ __global__ __launch_bounds__(256) void k_bonded_step(const LegDev* legs, BlockMa
     return;
   }
   const int where = (w << 20) | a;
-  g.frx[o] += to_fixed((double)fb.x, kForceScale, g.err, kSiteBonded, where, g.leg_index);
-  g.fry[o] += to_fixed((double)fb.y, kForceScale, g.err, kSiteBonded, where, g.leg_index);
-  g.frz[o] += to_fixed((double)fb.z, kForceScale, g.err, kSiteBonded, where, g.leg_index);
+  long long *fx = after_pairs ? g.fx : g.frx, *fy = after_pairs ? g.fy : g.fry, *fz = after_pairs ? g.fz : g.frz;
+  fx[o] += to_fixed((double)fb.x, kForceScale, g.err, kSiteBonded, where, g.leg_index);
+  fy[o] += to_fixed((double)fb.y, kForceScale, g.err, kSiteBonded, where, g.leg_index);
+  fz[o] += to_fixed((double)fb.z, kForceScale, g.err, kSiteBonded, where, g.leg_index);
 }
 
 // kick for one atom: returns v + dt F/m.  The total force (real-space terms
@@ -273,10 +274,10 @@ __global__ __launch_bounds__(256) void k_integrate(const LegDev* legs, BlockMap 
 
 }  // namespace
 
-void launch_bonded_step(hipStream_t s, const LegDev* d, const LegHost* h, int nl) {
+void launch_bonded_step(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool after_pairs) {
   BlockMap m;
   const int nb = make_map(m, nl, [&](int i) { return (int)(((long long)h[i].W * h[i].nba + 255) / 256); });
-  if (nb) hipLaunchKernelGGL(k_bonded_step, dim3(nb), dim3(256), 0, s, d, m);
+  if (nb) hipLaunchKernelGGL(k_bonded_step, dim3(nb), dim3(256), 0, s, d, m, after_pairs ? 1 : 0);
 }
 
 void launch_integrate(hipStream_t s, const LegDev* d, const LegHost* h, int nl, const long long* step,

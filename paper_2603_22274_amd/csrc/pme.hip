@@ -1247,9 +1247,7 @@ void launch_pme(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool e
     hipLaunchKernelGGL(k_spread, dim3(nb), dim3(256), 0, s, d, m);
   }
   // (forces of a step are taken on the side stream, beside the pair kernel)
-  long long pair_blocks = 0;
-  for (int i = 0; i < nl; ++i) pair_blocks += ((long long)h[i].W * h[i].nclus + 3) / 4;
-  launch_pme_fft(s, d, h, nl, 0, step_forces && pair_blocks >= kBesideBlocks);
+  launch_pme_fft(s, d, h, nl, 0, step_forces && pair_blocks(h, nl) >= kBesideBlocks);
   nb = make_map(m, nl, [&](int i) { return h[i].W * blocks_for((long long)h[i].npad, 64); });
   if (energy && step_forces) hipLaunchKernelGGL((k_gather<true, true>), dim3(nb), dim3(256), 0, s, d, m);
   else if (energy) hipLaunchKernelGGL((k_gather<true, false>), dim3(nb), dim3(256), 0, s, d, m);
