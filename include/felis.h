@@ -223,6 +223,12 @@ int felis_pme(felis_ctx* ctx, felis_leg* legs, int n_legs, int flags);
  * (bonds and torsions), RESTRAINT and TOTAL. */
 int felis_bonded(felis_ctx* ctx, felis_leg* legs, int n_legs, int flags);
 
+/* A whole force evaluation: felis_build_nlist (force = 0), felis_nonbonded,
+ * felis_pme and felis_bonded in one call with the same results; the PME grid
+ * is made on the context's second stream beside the list build and the pairs,
+ * and joined before the call's last kernels. */
+int felis_forces_energy(felis_ctx* ctx, felis_leg* legs, int n_legs, int flags);
+
 /* n_steps Langevin-middle steps ("Simulation protocol") for every window:
  * list check/rebuild, forces (nonbonded + PME + bonded), then
  * v += dt F/m; x += dt/2 v; v = a v + sqrt((1-a^2) kT/m) xi; x += dt/2 v;

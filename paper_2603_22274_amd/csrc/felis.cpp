@@ -807,6 +807,34 @@ int felis_bonded(felis_ctx* c, felis_leg* legs, int n_legs, int flags) {
   return launched(c);
 }
 
+int felis_forces_energy(felis_ctx* c, felis_leg* legs, int n_legs, int flags) {
+  std::vector<LegHost> hs;
+  int rc = prepare(c, legs, n_legs, hs);
+  if (rc) return rc;
+  const bool en = flags & FELIS_ENERGY;
+  const LegHost* h = hs.data();
+  if (en) launch_zero_energy(c->stream, c->d_legs, h, n_legs, 0, FELIS_E_TOTAL);
+  launch_check(c->stream, c->d_legs, h, n_legs, 0, false);
+  launch_sort_pack(c->stream, c->d_legs, h, n_legs);
+  // the grid needs only the sort and the pack: beside the list build and the
+  // pairs.  (Always the plain transform: the grid's FP32 sums decide the
+  // reciprocal energy's last digits.)
+  (void)hipEventRecord(c->ev_fork, c->stream);
+  (void)hipStreamWaitEvent(c->side, c->ev_fork, 0);
+  launch_pme_grid(c->side, c->d_legs, h, n_legs, false);
+  (void)hipEventRecord(c->ev_join, c->side);
+  launch_lists(c->stream, c->d_legs, h, n_legs);
+  mark(c, FELIS_PROF_PAIRS, false);
+  launch_pairs(c->stream, c->d_legs, h, n_legs, en ? 2 : 0);
+  mark(c, FELIS_PROF_PAIRS, true);
+  launch_corrections(c->stream, c->d_legs, h, n_legs, en);
+  (void)hipStreamWaitEvent(c->stream, c->ev_join, 0);
+  launch_pme_gather(c->stream, c->d_legs, h, n_legs, en, false);   // adds to the pair forces
+  launch_bonded(c->stream, c->d_legs, h, n_legs, en ? 2 : 0);
+  if (en) launch_finish_energy(c->stream, c->d_legs, h, n_legs, 0, FELIS_E_TOTAL);
+  return launched(c);
+}
+
 // Every energy component of every window of the batch (lists brought up to
 // date first); the window totals land in each leg's energy array.
 void energy_pass(felis_ctx* c, const std::vector<LegHost>& hs, int n_legs, bool from_word) {

@@ -431,6 +431,10 @@ void launch_bonded(hipStream_t s, const LegDev* d, const LegHost* h, int nl, int
 // step_forces: the gather stores each atom's force in frx/fry/frz (read by the
 // integrator) instead of adding it to fx/fy/fz
 void launch_pme(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool energy, bool step_forces = false);
+// its two parts: spreading and transform (beside: the pair kernel runs at the
+// same time), and the gather
+void launch_pme_grid(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool beside);
+void launch_pme_gather(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool energy, bool step_forces);
 // the step's bonded forces, added to fx/fy/fz (after_pairs: after the pair kernel
 // has stored there) or to frx/fry/frz (after the gather has)
 void launch_bonded_step(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool after_pairs);

@@ -1231,7 +1231,7 @@ void launch_pme_fft(hipStream_t s, const LegDev* d, const LegHost* h, int nl, in
   fft_pass<0, 6>(s, d, h, nl, beside);
 }
 
-void launch_pme(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool energy, bool step_forces) {
+void launch_pme_grid(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool beside) {
   BlockMap m;
   auto bricks = [&](int bx, int by, int bz) {
     return make_map(m, nl, [&](int i) {
@@ -1246,13 +1246,23 @@ void launch_pme(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool e
     nb = bricks(kBX, kBY, kBZ);
     hipLaunchKernelGGL(k_spread, dim3(nb), dim3(256), 0, s, d, m);
   }
-  // (forces of a step are taken on the side stream, beside the pair kernel)
-  launch_pme_fft(s, d, h, nl, 0, step_forces && pair_blocks(h, nl) >= kBesideBlocks);
-  nb = make_map(m, nl, [&](int i) { return h[i].W * blocks_for((long long)h[i].npad, 64); });
+  launch_pme_fft(s, d, h, nl, 0, beside && pair_blocks(h, nl) >= kBesideBlocks);
+}
+
+void launch_pme_gather(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool energy, bool step_forces) {
+  BlockMap m;
+  const int nb = make_map(m, nl, [&](int i) { return h[i].W * blocks_for((long long)h[i].npad, 64); });
+  if (!nb) return;
   if (energy && step_forces) hipLaunchKernelGGL((k_gather<true, true>), dim3(nb), dim3(256), 0, s, d, m);
   else if (energy) hipLaunchKernelGGL((k_gather<true, false>), dim3(nb), dim3(256), 0, s, d, m);
   else if (step_forces) hipLaunchKernelGGL((k_gather<false, true>), dim3(nb), dim3(256), 0, s, d, m);
   else hipLaunchKernelGGL((k_gather<false, false>), dim3(nb), dim3(256), 0, s, d, m);
+}
+
+void launch_pme(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool energy, bool step_forces) {
+  // (forces of a step are taken on the side stream, beside the pair kernel)
+  launch_pme_grid(s, d, h, nl, step_forces);
+  launch_pme_gather(s, d, h, nl, energy, step_forces);
 }
 
 }  // namespace felis

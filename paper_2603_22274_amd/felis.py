@@ -92,6 +92,7 @@ def lib():
         'felis_nonbonded': (C.c_int, [vp, P(FelisLeg), C.c_int, C.c_int]),
         'felis_pme': (C.c_int, [vp, P(FelisLeg), C.c_int, C.c_int]),
         'felis_bonded': (C.c_int, [vp, P(FelisLeg), C.c_int, C.c_int]),
+        'felis_forces_energy': (C.c_int, [vp, P(FelisLeg), C.c_int, C.c_int]),
         'felis_step': (C.c_int, [vp, P(FelisLeg), C.c_int, C.c_int, C.c_double, C.c_double, C.c_double]),
         'felis_ukn': (C.c_int, [vp, P(FelisLeg), vp, C.c_int, vp, vp, vp, C.c_int64, C.c_int64, vp,
                                 C.c_double, vp, C.c_int64]),
@@ -465,10 +466,8 @@ def bonded(ctx, legs, energy=True):
 
 def forces_and_energy(ctx, legs, energy=True):
     """Full force evaluation (list check, real space, PME, bonded)."""
-    build_nlist(ctx, legs)
-    nonbonded(ctx, legs, energy)
-    pme(ctx, legs, energy)
-    bonded(ctx, legs, energy)
+    arr = _batch(legs)
+    ctx.check(lib().felis_forces_energy(ctx.h, arr, len(legs), ENERGY if energy else 0))
 
 
 def step(ctx, legs, n_steps, dt=0.002, temperature=300.0, gamma=0.5):
