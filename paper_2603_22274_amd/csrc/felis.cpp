@@ -911,7 +911,7 @@ int felis_step(felis_ctx* c, felis_leg* legs, int n_legs, int n_steps, double dt
     launch_sort_pack(c->stream, c->d_legs, hs.data(), n_legs);
     // reciprocal space needs only the cell sort and the packed coordinates
     // and parameters: it runs on the side stream beside the list build and the
-    // pair kernel, and stores its forces apart (frx..), with the bonded ones
+    // pair kernel, and stores its forces apart (frx..)
     (void)hipEventRecord(c->ev_fork, c->stream);
     (void)hipStreamWaitEvent(c->side, c->ev_fork, 0);
     mark(c, FELIS_PROF_PME, false, c->side);
