@@ -817,8 +817,8 @@ int felis_forces_energy(felis_ctx* c, felis_leg* legs, int n_legs, int flags) {
   launch_check(c->stream, c->d_legs, h, n_legs, 0, false);
   launch_sort_pack(c->stream, c->d_legs, h, n_legs);
   // the grid needs only the sort and the pack: beside the list build and the
-  // pairs.  (Always the plain transform: the grid's FP32 sums decide the
-  // reciprocal energy's last digits.)
+  // pairs, by the plain transform (20 windows of 7,540 atoms: 675 us, 676 by the
+  // forms for a place beside the pairs: it ends before the energies do)
   (void)hipEventRecord(c->ev_fork, c->stream);
   (void)hipStreamWaitEvent(c->side, c->ev_fork, 0);
   launch_pme_grid(c->side, c->d_legs, h, n_legs, false);

@@ -37,7 +37,8 @@ constexpr int kXYThreads = 512;               // threads per whole-plane workgro
 // a workgroup of the transform gets a place only where pair workgroups end, and
 // those end one at a time: one wave and 64 registers on each of a CU's SIMDs.
 // Anything larger waits until no pair workgroup is left to take the place
-// first.  The *_beside forms fit (at most 256 threads, 64 registers).  With a
+// first.  The *_beside forms fit (at most 256 threads, 64 registers) and give the
+// same grid to the last bit.  With a
 // third of the pair workgroups or less in a second round the plain forms wait
 // little and end sooner: MD, us a pass, plain | beside: three served legs
 // 4,525 | 4,268, 20 windows of 7,540 atoms (4,720 pair workgroups) 1,524 | 1,472,

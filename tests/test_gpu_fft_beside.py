@@ -30,8 +30,6 @@ def test_step_forces_equal_a_force_evaluation(n, box, grid, windows):
     felis.step(ctx, [leg], 1)
     got = leg.forces().cpu().numpy()
     ctx.device_check()
-    # the same FP32 operations: at most a product and a sum rounded together here and apart there, a few
-    # roundings of 2^-24 in each of the transform's stages
-    err = np.sqrt(((got - want) ** 2).sum() / (want ** 2).sum())
-    assert err <= 2e-6, err
+    # a trajectory does not depend on the batch it runs in, so not on the launch's size either
+    assert np.array_equal(got, want), np.abs(got - want).max()
     ctx.close()
