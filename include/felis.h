@@ -49,7 +49,7 @@ extern "C" {
 #define FELIS_E_BOX (-3)         /* r_cut + skin >= half the shortest box edge */
 #define FELIS_E_CAPACITY (-4)    /* neighbour list capacity exceeded (see felis_check) */
 #define FELIS_E_OVERFLOW (-5)    /* fixed-point range exceeded or non-finite value */
-#define FELIS_E_NOCONV (-6)      /* MBAR reached max_iter */
+#define FELIS_E_NOCONV (-6)      /* MBAR reached max_iter or sums that are not finite */
 #define FELIS_E_UNSUPPORTED (-7) /* spline order != 4, softcore p != 1, grid > 128 ... */
 
 #define FELIS_FORCE_SCALE 4294967296.0   /* int64 force units per kcal/mol/A (2^32) */
@@ -401,7 +401,10 @@ int felis_mbar_work_size(int K, int64_t n_total, size_t* bytes);
  * (undamped) step of an iteration satisfies max|df| <= rel_tol * max(1, max|f|);
  * states with N_k = 0 follow from the converged denominators.  f_out (host)
  * [K] dimensionless free energies, gauge f_0 = 0; *iters the Newton
- * iterations used.  FELIS_E_NOCONV at max_iter or on a non-finite result.
+ * iterations used.  FELIS_E_NOCONV at max_iter, on a non-finite result or step,
+ * when u holds a NaN or a sample that no sampled state can hold (+inf at all of
+ * them), and when a self-consistent step is needed but the first sampled state
+ * has no weight left.
  * K in [2, 512].  Synchronises. */
 int felis_mbar(felis_ctx* ctx, const double* u, const int32_t* N_k, int K, int64_t n_total,
                double rel_tol, int max_iter, double* f_out, int* iters, void* work,

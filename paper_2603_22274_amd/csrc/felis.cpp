@@ -1142,7 +1142,7 @@ int felis_mbar(felis_ctx* c, const double* u, const int32_t* N_k, int K, int64_t
   if (!c) return FELIS_E_INVAL;
   int rc = launch_mbar(c->stream, u, N_k, K, n_total, rel_tol, max_iter, f_out, iters, work, work_bytes);
   if (rc == FELIS_E_INVAL) return fail(c, rc, "MBAR arguments (K in [2, 512], sum N_k = n_total, work size)");
-  if (rc == FELIS_E_NOCONV) return fail(c, rc, "MBAR did not converge within max_iter");
+  if (rc == FELIS_E_NOCONV) return fail(c, rc, "MBAR did not converge (max_iter reached, or sums that are not finite)");
   if (rc) return fail(c, rc, "MBAR device error");
   return launched(c);
 }
@@ -1162,7 +1162,7 @@ int felis_mbar_noalloc(felis_ctx* c, const double* u, const int32_t* N_k, int K,
   }
   int rc = launch_mbar_noalloc(c->device, c->stream, u, N_k, K, n_total, rel_tol, max_iter, f_out, iters);
   if (rc == FELIS_E_INVAL) return fail(c, rc, "MBAR arguments (K in [2, 512], sum N_k = n_total)");
-  if (rc == FELIS_E_NOCONV) return fail(c, rc, "MBAR did not converge within max_iter");
+  if (rc == FELIS_E_NOCONV) return fail(c, rc, "MBAR did not converge (max_iter reached, or sums that are not finite)");
   if (rc) return fail(c, rc, "MBAR device error");
   return launched(c);
 }

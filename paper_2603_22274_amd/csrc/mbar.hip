@@ -13,7 +13,10 @@
 // states follow from the converged denominators.  Converged when the
 // self-consistent update at the current iterate (the fixed-point iteration's
 // own change, relative to the gauge state) or a full Newton step is within
-// tol * max(1, max|f|); final gauge f_0 = 0.
+// tol * max(1, max|f|); final gauge f_0 = 0.  Sums that are not finite (u holds
+// a NaN, or a sample that no sampled state can hold), and a self-consistent
+// step where the gauge state has no weight to take it from, end the iteration
+// without a result.
 //
 // All device work is FP64 in a fixed summation order, so the result does not
 // depend on launch timing.  Two forms of the same iteration:
@@ -494,12 +497,19 @@ __global__ __launch_bounds__(512) void k_newton(FusedWork w, FusedArgs a) {
     st.phase = phase;
     write_state();
   };
-  // the self-consistent step from the sums g_k, relative to the gauge state
+  auto fail = [&]() {
+    st.code = FELIS_E_NOCONV;
+    st.phase = kPhDone;
+    write_state();
+  };
+  // the self-consistent step from the sums g_k, relative to the gauge state;
+  // false when that holds no weight
   auto sc_step = [&](double g) {
     if (mine) s_col[tid] = g;
     __syncthreads();
     const double gr = s_col[a.ref];
-    step = (mine && nk > 0.0 && tid != a.ref && gr > 0.0) ? -log(g) + log(gr) : 0.0;
+    step = (mine && nk > 0.0 && tid != a.ref) ? -log(g) + log(gr) : 0.0;
+    return gr > 0.0;
   };
   // the step just taken: converged, out of iterations, or on
   auto after_step = [&]() {
@@ -515,7 +525,7 @@ __global__ __launch_bounds__(512) void k_newton(FusedWork w, FusedArgs a) {
       if (++st.ls < 30) { next(f + st.t * step, kPhLine); return; }
       // no decrease found: a self-consistent step from the iterate's own sums
       st.t = 1.0;
-      sc_step(mine ? w.G[tid] : 0.0);
+      if (!sc_step(mine ? w.G[tid] : 0.0)) { fail(); return; }
       st.smax = block_max(fabs(step));
       f += step;
       const bool end = after_step();
@@ -525,7 +535,9 @@ __global__ __launch_bounds__(512) void k_newton(FusedWork w, FusedArgs a) {
     f = fe;
     if (after_step()) { finish(st.done); return; }
   }
-  // sums at the iterate f
+  // sums at the iterate f; the maxima below drop a NaN, so it is asked for by
+  // itself (a sample's logden is finite where its sampled states' weights are)
+  if (!isfinite(F)) { fail(); return; }
   ++st.it;
   st.t = 1.0;
   const double fscale = block_max(mine ? fmax(1.0, fabs(f)) : 1.0);
@@ -582,17 +594,12 @@ __global__ __launch_bounds__(512) void k_newton(FusedWork w, FusedArgs a) {
   }
   __syncthreads();
   if (newton) step = mine ? s_step[tid] : 0.0;
-  else sc_step(G);
+  else if (!sc_step(G)) { fail(); return; }
   if (tid == 0) s_bad = 0;
   __syncthreads();
   if (mine && !isfinite(step)) s_bad = 1;
   st.smax = block_max(fabs(step));
-  if (s_bad) {
-    st.code = FELIS_E_NOCONV;
-    st.phase = kPhDone;
-    write_state();
-    return;
-  }
+  if (s_bad) { fail(); return; }
   if (newton && st.smax > 1e-3) {                // backtracking on F while the step is large
     st.F = F;
     st.slope = slope;
@@ -703,6 +710,7 @@ int launch_mbar(hipStream_t s, const double* u, const int* N_k, int K, long long
   while (it < max_iter) {
     int rc = evaluate(s, u, w, K, N, f, Nk, true, ev);
     if (rc) return rc;
+    if (!std::isfinite(ev.F)) return FELIS_E_NOCONV;
     ++it;
     // the self-consistent update at this iterate, -ln(sum_n W_in) relative
     // to the gauge state: the change of f the fixed-point iteration would
@@ -738,9 +746,9 @@ int launch_mbar(hipStream_t s, const double* u, const int* N_k, int K, long long
       newton = slope < 0.0 || m == 0;
     }
     if (!newton) {                       // self-consistent step
+      if (!(ev.G[ref] > 0.0)) return FELIS_E_NOCONV;
       std::fill(step.begin(), step.end(), 0.0);
-      if (ev.G[ref] > 0.0)
-        for (int r = 0; r < m; ++r) step[idx[r]] = -std::log(ev.G[idx[r]]) + std::log(ev.G[ref]);
+      for (int r = 0; r < m; ++r) step[idx[r]] = -std::log(ev.G[idx[r]]) + std::log(ev.G[ref]);
     }
     double smax = 0.0;
     for (int k = 0; k < K; ++k) {
@@ -763,14 +771,14 @@ int launch_mbar(hipStream_t s, const double* u, const int* N_k, int K, long long
         if (!ok) t *= 0.5;
       }
       if (!ok) {                         // no decrease found: self-consistent step instead
+        if (!(ev.G[ref] > 0.0)) return FELIS_E_NOCONV;
         t = 1.0;
         smax = 0.0;
         std::fill(step.begin(), step.end(), 0.0);
-        if (ev.G[ref] > 0.0)
-          for (int r = 0; r < m; ++r) {
-            step[idx[r]] = -std::log(ev.G[idx[r]]) + std::log(ev.G[ref]);
-            smax = std::fmax(smax, std::fabs(step[idx[r]]));
-          }
+        for (int r = 0; r < m; ++r) {
+          step[idx[r]] = -std::log(ev.G[idx[r]]) + std::log(ev.G[ref]);
+          smax = std::fmax(smax, std::fabs(step[idx[r]]));
+        }
       }
     }
     double fmaxv = 0.0;
