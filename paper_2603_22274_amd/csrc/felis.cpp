@@ -33,7 +33,7 @@ struct Plan {
 struct Meta {          // facts read from the topology at felis_leg_init
   int nfree, nlig;
   int naw;             // alchemical-water atoms
-  int nba;             // atoms with bonded terms
+  int nba;             // atoms with a bond or a torsion
   int nmol;            // molecules (legs with a barostat; 0 otherwise)
   size_t work_bytes;
 };
@@ -188,7 +188,7 @@ int make_plan(felis_ctx* c, const felis_leg* L, Plan& P) {
   y.bid = put(2 * (size_t)std::max(h.nbonds, 1) * 4);
   y.tptr = put((n + 1) * 4);                      // per-atom torsion table (filled at set-up)
   y.tid = put(4 * (size_t)std::max(h.ntors, 1) * 4);
-  y.batoms = put(n * 4);                          // atoms with bonded terms (filled at set-up)
+  y.batoms = put(n * 4);                          // atoms with a bond or a torsion (filled at set-up)
   {
     // barostat: molecule table, per-window state, positions before a move
     const bool npt = L->pressure_bar > 0;
@@ -644,9 +644,7 @@ int felis_leg_init(felis_ctx* c, felis_leg* L) {
   std::vector<int> bij(2 * (size_t)h.nbonds);
   if (h.nbonds && hipMemcpy(bij.data(), L->bond_ij, bij.size() * 4, hipMemcpyDeviceToHost) != hipSuccess)
     return fail(c, FELIS_E_DEVICE, "bond copy failed");
-  std::vector<char> bonded(h.n, 0);     // atoms with bonded terms
-  if (h.has_rest)
-    for (int t = 0; t < 6; ++t) bonded[L->restraint_atoms[t]] = 1;
+  std::vector<char> bonded(h.n, 0);     // atoms with a bond or a torsion
   {
     // per-atom bond table for the step's bonded forces: for atom a, its
     // partners and bond indices in bond order

@@ -108,7 +108,7 @@ struct LegDev {
   const float *tors_k, *tors_phase;     // [ntors]
   const int* tors_n;                    // [ntors]
   const int *tptr, *tid;                // per-atom torsions: CSR [n + 1] over 4 t + (the atom's place in t)
-  const int* batoms;                    // [nba] atoms with a bond, a torsion or an anchor
+  const int* batoms;                    // [nba] atoms with a bond or a torsion
   int nba;
   const float* aoff;                    // [n] alchemical-water charge offsets (NULL: none)
   int naw;                              // alchemical-water atoms (nonzero offset)

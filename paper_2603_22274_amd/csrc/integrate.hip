@@ -117,19 +117,31 @@ __device__ __forceinline__ v3 bonded_force(const LegDev& g, int w, int a) {
   return F;
 }
 
-// items: window x bonded atom (any atom with a bond, a torsion or an anchor):
-// adds its bonded terms to its pair force or its reciprocal-space force,
-// after that has been stored.  A kernel of its own, ahead of the integrator: the partners'
-// positions must be those of the step's start, and the integrator overwrites
-// them (summed there, an atom whose partner's wave had already stored saw the
-// new position).
+// items: window x (atom with a bond or a torsion, then the six anchors of the
+// restraint): adds the atom's bonded terms to its pair force or its
+// reciprocal-space force, after that has been stored.  The atoms are a table
+// made at set-up, like the bonds; the anchors are the descriptor's of the call,
+// and one that the table or an earlier anchor names already is left out.  A
+// kernel of its own, ahead of the integrator: the partners' positions must be
+// those of the step's start, and the integrator overwrites them (summed there,
+// an atom whose partner's wave had already stored saw the new position).
 __global__ __launch_bounds__(256) void k_bonded_step(const LegDev* legs, BlockMap map, int after_pairs) {
   const int leg = find_leg(map, blockIdx.x);
   const LegDev& g = legs[leg];
   const long long i = (long long)(blockIdx.x - map.start[leg]) * blockDim.x + threadIdx.x;
-  if (i >= (long long)g.W * g.nba) return;
-  const int w = (int)(i / g.nba);
-  const int a = g.batoms[i - (long long)w * g.nba];
+  const int per = g.nba + (g.has_rest ? 6 : 0);
+  if (i >= (long long)g.W * per) return;
+  const int w = (int)(i / per);
+  const int k = (int)(i - (long long)w * per);
+  int a;
+  if (k < g.nba) {
+    a = g.batoms[k];
+  } else {
+    a = g.ranch[k - g.nba];
+    bool named = g.bptr[a] != g.bptr[a + 1] || g.tptr[a] != g.tptr[a + 1];
+    for (int t = 0; t < k - g.nba; ++t) named |= g.ranch[t] == a;
+    if (named) return;
+  }
   const v3 fb = bonded_force(g, w, a);
   const size_t o = (size_t)w * g.n + a;
   if (g.plain) {
@@ -276,7 +288,9 @@ __global__ __launch_bounds__(256) void k_integrate(const LegDev* legs, BlockMap 
 
 void launch_bonded_step(hipStream_t s, const LegDev* d, const LegHost* h, int nl, bool after_pairs) {
   BlockMap m;
-  const int nb = make_map(m, nl, [&](int i) { return (int)(((long long)h[i].W * h[i].nba + 255) / 256); });
+  const int nb = make_map(m, nl, [&](int i) {
+    return (int)(((long long)h[i].W * (h[i].nba + (h[i].has_rest ? 6 : 0)) + 255) / 256);
+  });
   if (nb) hipLaunchKernelGGL(k_bonded_step, dim3(nb), dim3(256), 0, s, d, m, after_pairs ? 1 : 0);
 }
 
