@@ -496,12 +496,15 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 1 ? 6 : 5) void k_build(const 
     near = near && fabsf(ri[d]) + incl + 0.02f < 0.5f * Lf[d];
   }
   float ni = __fmaf_rn(ri[0], ri[0], __fmaf_rn(ri[1], ri[1], ri[2] * ri[2]));
+  // The expanded form rounds by up to 27 2^-24 (|r_i| + r_list)^2 where it counts:
+  // 7 roundings of |r_i|^2 and |r_j|^2, 5 of sums within (|r_i| + |r_j|)^2, |r_j| <
+  // |r_i| + r_list.  Held below the margin of 0.01 A, 0.02 r_list A^2 (2^-18 (|r_i|^2
+  // + r_list^2) is above that bound): |r_i| up to some 230 A at r_list = 10; wider
+  // pairs, in sparse systems of large boxes, take the image per pair
+  near = near && (ni + inc2) * 3.8146973e-6f < inc2 - rlist * rlist;
   const bool real = si < n && ni < kFar;        // false for a padding slot and for a NaN position
   const bool shift = __ballot(si < n && !near) == 0ull;
   ni = real ? ni : kFar;
-  // (in the frame of the first atom |r| < r_list + the pair's extent where it
-  // counts, so the FP32 error of the expanded form stays below 1e-3 A^2, far
-  // inside the margin of 0.01 A, 0.2 A^2)
   const float am = !real ? 0.f : row == 0 ? -2.0f * ri[0] : row == 1 ? -2.0f * ri[1] : row == 2 ? -2.0f * ri[2] : 1.0f;
   if (tid < 16) {
     s_xi[tid] = make_float4(xi[0], xi[1], xi[2], real ? 0.f : kFar);
@@ -675,7 +678,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 1 ? 6 : 5) void k_build(const 
               m[k] = __builtin_amdgcn_alignbit(v, __float_as_uint(d[0]), 31);
             }
           } else {
-            // small boxes and spread clusters: the nearest image per pair
+            // small boxes and wide cluster pairs: the nearest image per pair
             unsigned mask = 0;
 #pragma unroll 4
             for (int ii = 0; ii < 16; ++ii) {
