@@ -1,8 +1,8 @@
 """Summaries of rocprofv3 output databases (kernel traces and PMC counters).
 
     python -m paper_2603_22274_amd.profiling stats <trace_dir> [n]
-    python -m paper_2603_22274_amd.profiling traffic <fetch_dir> <write_dir> <kernel-substring>
-    python -m paper_2603_22274_amd.profiling counters <pmc_dir> <kernel-substring> ...
+    python -m paper_2603_22274_amd.profiling traffic <fetch_dir> <write_dir> <kernel>
+    python -m paper_2603_22274_amd.profiling counters <pmc_dir> <kernel> ...
     python -m paper_2603_22274_amd.profiling profiles <run_dir> <profiles_dir> [workload]
 
     python -m paper_2603_22274_amd.profiling steps <trace_dir> [min_pair_us]
@@ -28,6 +28,7 @@ import glob
 import hashlib
 import json
 import os
+import re
 import sqlite3
 import sys
 
@@ -81,7 +82,6 @@ def step_breakdown(trace_dir, min_pair_us=0.0, max_step_us=20000.0):
     delimit steps; intervals longer than ``max_step_us`` (host work between
     calls) are skipped."""
     import collections
-    import re
     rows = _kernel_rows(trace_dir)
 
     def nm(n):
@@ -155,11 +155,17 @@ def timeline(trace_dir, host_gap_us=100.0, after_gap_ms=0.0):
             "busy_us_per_md_step": busy / n / 1e3}
 
 
+def _is(kernel, name):
+    """Whether ``name``, a full kernel name, holds ``kernel`` as a name of its own (template arguments may
+    be left out at the end): ``k_spread`` is not ``k_spread_wide``."""
+    return re.search(r'(?<!\w)' + re.escape(kernel) + r'(?!\w)', name) is not None
+
+
 def _counter(con, kernel_sub):
     """Mean per dispatch over the kernel's largest launches (the workload's
     own: a run also launches the kernel for smaller preparation legs)."""
     rows = [(g, v) for (n, g, v) in con.execute("select kernel_name, grid_size, value from counters_collection")
-            if kernel_sub in n]
+            if _is(kernel_sub, n)]
     if not rows:
         return None, 0
     gmax = max(g for g, _ in rows)
@@ -193,24 +199,24 @@ def traffic(fetch_dir, write_dir, kernel_sub, copy_bytes=256 << 20):
 
 def counters(pmc_dir, kernels):
     """Per-dispatch averages of every counter collected in ``pmc_dir`` for the
-    kernels whose names contain one of ``kernels``."""
+    kernels named by ``kernels``."""
     con = _db(pmc_dir)
     rows = con.execute("select kernel_name, grid_size, counter_name, value from counters_collection").fetchall()
     gmax = {}
     for name, g, cname, v in rows:
         for k in kernels:
-            if k in name:
+            if _is(k, name):
                 gmax[k] = max(gmax.get(k, 0), g)
     out = {}
     for name, g, cname, v in rows:
         for k in kernels:
-            if k in name and g == gmax[k]:       # the workload's own launches
+            if _is(k, name) and g == gmax[k]:       # the workload's own launches
                 out.setdefault(k, {}).setdefault(cname, []).append(v)
     return {k: {c: sum(v) / len(v) for c, v in d.items()} for k, d in out.items()}
 
 
 _CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), 'csrc')
-PAIR_SOURCES = ('nonbonded.hip', 'erfc_coeffs.h', 'felis_internal.h')
+PAIR_SOURCES = ('nonbonded.hip', 'erfc_coeffs.h', 'erfc_coeffs_fp64.h', 'restraint.h', 'felis_internal.h')
 # passes of an MD step's transform, by itself and beside a large pair kernel
 FFT_KERNELS = tuple(f'k_fft{b}{a}' for b in ('', '_beside')
                     for a in ('<0, 0, 32>', '<1, 0, 32>', '<2, 3, 32>', '<1, 1, 32>', '<0, 6, 32>')) + (
@@ -225,6 +231,7 @@ WORKLOADS = {
                   "--no-cpu-baseline --no-per-window --serve-legs 0 --ukn-frames 0 --ddg-segment '' "
                   "--copy-calibration", 'k_pairs<0>', 20 * 7540 * 3 * 8),
 }
+SPREAD_KERNEL = {'complex42': 'k_spread_wide', 'solvent20': 'k_spread'}      # by the launch's number of bricks
 WORKLOADS_SIZE = {'complex42': (42, 70527, 96 ** 3), 'solvent20': (20, 7540, 48 ** 3)}
 _PASSES = {
     'A': 'SQ_WAVES SQ_WAVE_CYCLES SQ_BUSY_CYCLES SQ_WAIT_ANY SQ_WAIT_INST_ANY SQ_ACTIVE_INST_VALU '
@@ -277,7 +284,7 @@ def write_profiles(out_dir, prof_dir, workload='complex42'):
     W, N, K3 = WORKLOADS_SIZE[workload]
     npair = (W + 1) // 2
     alg = {kernel: 48 * W * N,
-           'k_spread': W * (32 * N + 4 * K3),                 # stencils + charges in, own grid component out
+           SPREAD_KERNEL[workload]: W * (32 * N + 4 * K3),    # stencils + charges in, own grid component out
            **{k: npair * K3 * 16 for k in FFT_KERNELS},
            'k_gather<false, true>': W * (4 * K3 + 56 * N),    # own grid component, stencils + charges, forces
            'k_integrate': W * N * 76, 'k_pack<true>': W * N * 48, 'k_build': None}
@@ -300,7 +307,8 @@ def write_profiles(out_dir, prof_dir, workload='complex42'):
         fh.write("\n".join(txt) + "\n")
     # per-axis FFT passes of the step: 32 lines per workgroup (the u_kn passes,
     # with 16 lines and a larger grid, are other launches)
-    ks = [kernel, 'k_build', 'k_spread', 'k_gather<false, true>', *FFT_KERNELS, 'k_integrate', 'k_pack<true>']
+    ks = [kernel, 'k_build', SPREAD_KERNEL[workload], 'k_gather<false, true>', *FFT_KERNELS, 'k_integrate',
+          'k_pack<true>']
     A = counters(pre + 'A', ks)
     B = counters(pre + 'B', ks)
     lines = [f"VALU counters per dispatch, bench.py workload ({desc}), MI355X.",
