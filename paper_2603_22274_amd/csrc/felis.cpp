@@ -378,7 +378,9 @@ int prepare(felis_ctx* c, const felis_leg* legs, int n_legs, std::vector<LegHost
 // MD, us a pass, bonded forces behind the gather | behind the pairs: 12 windows
 // of 668 atoms (252 workgroups) 490 | 463, one window of 70,527 atoms (2,204)
 // 647 | 628, NPT, 20 windows of 7,540 (4,720) 1,735 | 1,706, three served legs
-// (19,500) 4,262 | 4,341, 42 windows of 70,527 (92,600) 11,770 | 12,070.
+// (19,500) 4,262 | 4,341, 42 windows of 70,527 (92,600) 11,770 | 12,070.  Near the
+// line, us a step: 26 windows of 7,540 (6,130) 335 | 338, 35 (8,250) 441 | 445; 4
+// windows of 70,527 (8,816) 469 | 459, 7 (15,430) 796 | 782, 10 (22,040) 990 | 1,008.
 constexpr long long kLongPairs = 8192;
 
 // Records an event for timer t when profiling is on (start when stop == false).

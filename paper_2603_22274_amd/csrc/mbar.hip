@@ -219,7 +219,10 @@ bool solve(std::vector<double>& A, std::vector<double>& b, int m) {
 
 // ---- the fused form
 
-constexpr int kFusedStates = 80;  // 5 tiles of 16; the Newton system of 79 free states fits in 64 KB of LDS
+// Most states of the fused form: 5 tiles of 16, with which a wave of k_eval holds
+// 20 states' values and 5 tiles' sums in registers, its weights take 41 KB of LDS
+// and the Newton system of 79 free states 51 KB.  More take the general form
+constexpr int kFusedStates = 80;
 constexpr int kEvalBlocks = 512;  // two per CU: later rounds of a block keep its sums in registers
 constexpr int kDirect = 4;        // up to this many blocks' sums k_newton adds up itself
 
@@ -296,7 +299,7 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // within a tile and rows are an odd number of tiles long, so the writes (64
 // samples, one state) meet in 2 of 32 bank pairs and the reads in none.
 // Bound: reading u (8 K N bytes) and one FP64 exponential an element.  42 x
-// 84,000: 41 us an evaluation with its reduction (separate denominators,
+// 84,000: 43 us an evaluation with its reduction (separate denominators,
 // weights and products through memory: 277 us), 27 us for k_newton.
 template <int T>
 __global__ __launch_bounds__(256) void k_eval(const double* __restrict__ u, FusedWork w, FusedArgs a) {

@@ -20,7 +20,10 @@ constexpr int kTabOf = 4096;                  // candidates per table window in 
 // pair's set-up and the round's (a sixth of a pair's work), so one wave does
 // the least work and four end soonest where the pairs alone do not fill the
 // chip.  One | four waves: 504 pairs 15.8 | 10.0 us, 9,440 (20 windows of 7,540
-// atoms) 108 | 82, 39,000 245 | 290, 185,000 (42 windows of 70,527) 786 | 1418
+// atoms) 108 | 82, 39,000 245 | 290, 185,000 (42 windows of 70,527) 786 | 1418.
+// Near the line, us a step: 7,540 atoms, 12,300 pairs 361 | 340, 16,500 441 | 431,
+// 21,200 537 | 540; 70,527 atoms, 13,200 378 | 404, 17,600 469 | 487; 668 atoms, 8,400
+// 244 | 254, 16,400 414 | 452
 constexpr int kFewPairs = 16384;
 constexpr float kFar = 1.0e30f;               // squared distance that no test passes
 

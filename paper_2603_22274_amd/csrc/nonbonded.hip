@@ -559,9 +559,10 @@ __device__ __forceinline__ void pair_energy_fp64(const EnergyLeg& g, const Energ
   const double r = sqrt(r2);
   if (!(r < g.rc)) return;
   const double qj = (double)q1 * (lj ? g.lam_e : 1.0) + (1.0 - g.lam_e) * (double)off;
-  // erfc(alpha r) by the fit of erfc_coeffs_fp64.h (within 1e-15; alpha r_c <=
-  // 3.5): without the range branches of the library's erfc, which a wave of
-  // distances from 1 to 10 A takes all of
+  // erfc(alpha r) by the fit of erfc_coeffs_fp64.h (fit 3e-16, evaluated in FP64
+  // 1.4e-15, and an ulp or two more for the refined reciprocal; alpha r_c <= 3.5):
+  // without the range branches of the library's erfc, which a wave of distances
+  // from 1 to 10 A takes all of
   const double rinv = rsqrt_fp64(r2);
   const double xa = g.alpha * r;
   const double t = rcp_fp64(fma(FELIS_ERFC64_P, xa, 1.0));

@@ -13,7 +13,7 @@
 // FFT: Stockham autosort, radices 8/12/4/2/3/5.  Grids whose x-y planes fit in
 // LDS twice (gfx950: 160 KB per workgroup, so up to ~100 x 100 points) are
 // transformed by whole planes (x then y in one workgroup), otherwise one
-// kernel per axis with 16 lines per workgroup
+// kernel per axis with 16 or, in launches with many, 32 lines per workgroup
 // ([element][line] layout, coalesced loads for every axis).  The inverse
 // transform is conj(DFT(conj(.))).  The z pass fuses forward transform,
 // multiplication by G and inverse transform.
@@ -43,6 +43,8 @@ constexpr int kXYThreads = 512;               // threads per whole-plane workgro
 // little and end sooner: MD, us a pass, plain | beside: three served legs
 // 4,525 | 4,268, 20 windows of 7,540 atoms (4,720 pair workgroups) 1,524 | 1,472,
 // one window of 70,527 atoms (2,204) 763 | 772, 12 windows of 668 atoms 536 | 546.
+// Near the line, us a step: 13 windows of 7,540 (3,065) 215 | 215, 18 (4,244) 266 |
+// 260; 100 windows of 668 (2,100) 170 | 162, 146 (3,066) 218 | 204.
 constexpr int kBesideBlocks = 3072;
 
 __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
@@ -597,7 +599,11 @@ constexpr int kSpreadRanges = 256;             // candidate ranges at a time (on
 // fewest bricks for k_spread_wide: eight a compute unit.  Below, one brick's
 // time counts and k_spread's 256 threads a brick of a quarter the size end
 // sooner: 20 windows on 48^3 (540 bricks) 34 us against 45, one window on
-// 96^3 (216) 18 against 27
+// 96^3 (216) 18 against 27.  In a step it also counts how the bricks lie beside
+// the pairs: us a step, small | wide bricks, 48^3: 9 windows (243 bricks) 179 | 183,
+// 26 (702) 340 | 327, 60 (1,620) 683 | 676, 76 (2,052) 830 | 820; 20^3: 200 (1,600)
+// 253 | 259, 300 (2,400) 357 | 363, 500 (4,000) 518 | 501; 96^3: 2 (432) 293 | 277, 7
+// (1,512) 795 | 732, 10 (2,160) 1,090 | 991
 constexpr int kWideBlocks = 2048;
 constexpr int kSpreadCellOf = 1024;            // candidates per table window in spreading
 constexpr int kSpreadChunk = 128;              // atoms per compact task list in spreading
@@ -1016,7 +1022,7 @@ __global__ __launch_bounds__(256, 8) void k_spread_wide(const LegDev* legs, Bloc
 // 42 windows of 70,527 atoms on 96^3: 232 us alone; 365 us when each block of
 // 64 atoms staged the box around their stencils in LDS from the complex grid
 // (16 points a thread, each with its index arithmetic).  Beside the pair
-// kernel inside a step: 1,290 -> 300 us.
+// kernel inside a step, where it waits for places: 1,290 -> 360 us.
 // STEP: store the force in frx/fry/frz (the integrator adds it to the
 // real-space force) instead of adding it to fx/fy/fz
 template <bool ENERGY, bool STEP>

@@ -447,7 +447,7 @@ __device__ __forceinline__ void ukn_const(const LegDev& g, double* out) {
 // lanes take one lambda_vdw value each.  The first block sums the charges'
 // constants (a serial pass of its own otherwise).  42 frames of 70,527 atoms, 50 ligand
 // atoms, 20 values: 525 + 45 us with a lane per atom looping over the ligand
-// and the values; 75 us so (beside the transform on its own stream).
+// and the values; 120 us so, beside the transform on its own stream.
 __global__ __launch_bounds__(256) void k_ukn_pairs(const LegDev* legs, UknArgs A, double* cst) {
   const LegDev& g = legs[0];
   if (blockIdx.x == 0) {                  // uniform
