@@ -101,7 +101,7 @@ typedef struct felis_leg {
   int32_t n_waters;
   const int32_t* water_ohh;      /* (dev) [n_waters][3] O, H1, H2 (rigid, SETTLE) */
   double d_oh, d_hh;             /* rigid water geometry, A */
-  int32_t has_restraint;         /* 1: Boresch restraint on the anchors below */
+  int32_t has_restraint;         /* 1: Boresch restraint on the anchors below (read at every call) */
   int32_t restraint_atoms[6];    /* P1 P2 P3 L1 L2 L3 */
   double restraint_g0[6];        /* r0 (A), thetaA0, thetaB0, phiA0, phiB0, phiC0 (rad) */
   double restraint_k[6];         /* k_r (kcal/mol/A^2), k_theta x2 (kcal/mol/rad^2), k_phi x3 (kcal/mol) */
